@@ -430,9 +430,7 @@ void refresh_level_scalars(amg_s* M, int l, const double* d_user, hipStream_t s)
 void coarse_factor(amg_s* M, Level& L, hipStream_t s) {
   if (L.n_term == 0) return;
   const bsr_s* A = L.A;
-  const size_t bytes = static_cast<size_t>(L.t_total) * sizeof(double);
-  HIP_CHECK(hipMemsetAsync(L.tL.p, 0, bytes, s));
-  HIP_CHECK(hipMemsetAsync(L.tY.p, 0, bytes, s));
+  HIP_CHECK(hipMemsetAsync(L.tL.p, 0, static_cast<size_t>(L.t_total) * sizeof(double), s));
   const dim3 eg(std::max(L.t_max_rows, 1), L.n_term);
   if (A->dtype == BLKAMG_F64)
     expand_dense_kernel<double><<<eg, 64, 0, s>>>(L.t_row0.p, L.t_nrows.p, L.t_mat_off.p, L.bs, A->rowptr, A->colidx,
@@ -442,16 +440,13 @@ void coarse_factor(amg_s* M, Level& L, hipStream_t s) {
                                                  static_cast<const float*>(A->val), L.tL.p);
   HIP_CHECK(hipGetLastError());
   const int nt = L.t_max_tiles;
-  for (int k = 0; k < nt; ++k) {
-    chol_panel_kernel<<<dim3(nt - k, L.n_term), 256, 0, s>>>(L.tL.p, L.t_mat_off.p, L.t_ndof.p, k, M->flags.p);
-    const int m = nt - k - 1;
-    if (m > 0) chol_update_kernel<<<dim3(m * (m + 1) / 2, L.n_term), 256, 0, s>>>(L.tL.p, L.t_mat_off.p, L.t_ndof.p, k);
+  for (int k = -1; k < nt; ++k) {
+    const int m = nt - k - 1;  // trailing tiles, right-hand sides and the finished row of Y
+    const int tiles = k < 0 ? 1 : m * (m + 1) / 2 + m * (k + 1) + k;
+    if (tiles > 0)
+      chol_inverse_kernel<<<dim3(tiles, L.n_term), 256, 0, s>>>(L.tL.p, L.tY.p, L.tYt.p, L.t_mat_off.p, L.t_ndof.p, k,
+                                                              M->flags.p);
   }
-  HIP_CHECK(hipGetLastError());
-  tri_inverse_col_kernel<<<dim3(nt, L.n_term), 256, 0, s>>>(L.tL.p, L.tY.p, L.t_mat_off.p, L.t_ndof.p);
-  HIP_CHECK(hipGetLastError());
-  transpose_dense_kernel<<<dim3(vgrid(static_cast<size_t>(L.t_max_nn)), L.n_term), 256, 0, s>>>(
-      L.tY.p, L.tYt.p, L.t_mat_off.p, L.t_ndof.p);
   HIP_CHECK(hipGetLastError());
 }
 
