@@ -42,7 +42,7 @@ struct Level {
   int n = 0, bs = 0;                   // scalar dofs, block size
   DevBuf<int32_t> d_act_off;           // block-row offsets of the smoothed segments
   DevBuf<uint16_t> d_row_seg;          // segment of each smoothed row (several segments only)
-  SegGrid lgrid;                       // Lanczos dots over the smoothed dofs
+  SegGrid lgrid;                       // Lanczos, judge and feature reductions over the smoothed dofs
   // A P of this level (rows of A_act x rows of the next level), kept by the Galerkin plan
   // of the next level's operator: a view over the plan's arrays (refilled at each use),
   // and the stamps of A and P when the Galerkin pass last formed it (0 = never)
@@ -182,17 +182,35 @@ __global__ __launch_bounds__(256) void reduce_kernel(const double* __restrict__ 
   }
 }
 
+// Many partials are first summed to 256 (fixed chunks); n becomes the number left.
+const double* reduce_chunks(amg_s* M, int& n, hipStream_t s) {
+  if (n <= 4096) return M->partial.p;
+  const int chunks = 256;
+  reduce_chunks_kernel<<<chunks, 256, 0, s>>>(M->partial.p, n, (n + chunks - 1) / chunks, M->partial2.p);
+  HIP_CHECK(hipGetLastError());
+  n = chunks;
+  return M->partial2.p;
+}
+
 // Deterministic sum of n partials (fixed chunking, fixed order), then `op`.
+template <class Op>
+__global__ __launch_bounds__(256) void sum_finish_kernel(const double* __restrict__ partial, int n, Op op) {
+  __shared__ double lds[4];
+  double v = 0.0;
+  for (int i = threadIdx.x; i < n; i += 256) v += partial[i];
+  const double s = block_sum_256(v, lds);
+  if (threadIdx.x == 0) op(0, 0, s);
+}
+
+template <class Op>
+void sum_finish(amg_s* M, int n, const Op& op, hipStream_t s) {
+  const double* src = reduce_chunks(M, n, s);
+  sum_finish_kernel<Op><<<1, 256, 0, s>>>(src, n, op);
+  HIP_CHECK(hipGetLastError());
+}
+
 void reduce(amg_s* M, int n, double* dst, int op, hipStream_t s) {
-  const double* src = M->partial.p;
-  if (n > 4096) {
-    const int chunks = 256;
-    const int chunk = (n + chunks - 1) / chunks;
-    reduce_chunks_kernel<<<chunks, 256, 0, s>>>(M->partial.p, n, chunk, M->partial2.p);
-    HIP_CHECK(hipGetLastError());
-    src = M->partial2.p;
-    n = chunks;
-  }
+  const double* src = reduce_chunks(M, n, s);
   reduce_kernel<<<1, 256, 0, s>>>(src, n, dst, op, M->pcg_s.p);
   HIP_CHECK(hipGetLastError());
 }
@@ -230,12 +248,18 @@ void build_grid(amg_s* M, SegGrid& g, const std::vector<int64_t>& dof_off, int c
   }
 }
 
+// op of the sums of M->partial over each segment's chunks, nr columns
+template <class Op>
+void seg_finish(amg_s* M, const SegGrid& g, int nr, const Op& op, hipStream_t s) {
+  seg_finish_kernel<Op><<<g.nseg * nr, 256, 0, s>>>(M->partial.p, g.ptr.p, nr, op);
+  HIP_CHECK(hipGetLastError());
+}
+
 template <int NR, class T, class Op, class TB = T>
 void seg_reduce(amg_s* M, const SegGrid& g, const T* a, const TB* b, const Op& op, hipStream_t s) {
   if (g.nseg == 0) return;
   if (g.nchunk > 0) seg_dot_kernel<NR, T, TB><<<g.nchunk, 256, 0, s>>>(a, b, g.lo.p, g.hi.p, M->partial.p);
-  seg_finish_kernel<Op><<<g.nseg * NR, 256, 0, s>>>(M->partial.p, g.ptr.p, NR, op);
-  HIP_CHECK(hipGetLastError());
+  seg_finish(M, g, NR, op, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -277,7 +301,10 @@ void finalize_level(amg_s* M, Level& L) {
   }
   std::vector<int64_t> doff;
   for (int t = 0; t <= L.n_act; ++t) doff.push_back(static_cast<int64_t>(L.seg_off[t]) * L.bs);
-  build_grid(M, L.lgrid, doff, 8192, kFeatStats);
+  // 512 block rows a chunk: two rows per thread, so that a level of a few thousand rows
+  // already spreads over the chip (chunks of 8192 dofs left 100 workgroups and 10 us per
+  // dot product at 64^3)
+  build_grid(M, L.lgrid, doff, 512 * L.bs, kFeatStats * kFeatSplit);
   const int ns = L.n_seg();
   L.n_term = ns - L.n_act;
   std::vector<int32_t> row0, nrows, ndof, dof_off{0};
@@ -360,53 +387,62 @@ void compute_dinv(amg_s* M, Level& L, hipStream_t s) {
   HIP_CHECK(hipGetLastError());
 }
 
+template <class TV>
+TV* lanczos_vec(Level& L, int t, size_t n) {
+  if constexpr (sizeof(TV) == 8) {
+    if (L.lz[t].n < n) L.lz[t].alloc(n);
+    return reinterpret_cast<TV*>(L.lz[t].p);
+  } else {
+    if (L.lzf[t].n < n) L.lzf[t].alloc(n);
+    return reinterpret_cast<TV*>(L.lzf[t].p);
+  }
+}
+
 // k-step Lanczos on D^-1 A in the D inner product, one recurrence per smoothed
-// segment of level l; results into sc[l][segment].
+// segment of level l; results into sc[l][segment].  The vectors stay unnormalised
+// (U = b u, Y = b y) and the factors go into the next product's epilogue, so a step is the
+// product (with U.wy, for one segment), one pass for the orthogonalisation with its norm,
+// and the two sums: four or five launches and no pass for scaling or dot products alone
+// (64^3 FP64: 142 -> 128 us a fine step, 49 -> 29 us on the next level).
 template <int BS, class TV>
 void lanczos_bs(amg_s* M, int l, hipStream_t s) {
   Level& L = *M->lv[l];
   const bsr_s* A = L.A_act.get();
   const int nbr = A->nbr;
   const size_t n = static_cast<size_t>(nbr) * BS;
-  TV* V[6];
-  for (int t = 0; t < 6; ++t) {
-    if constexpr (sizeof(TV) == 8) {
-      if (!L.lz[t].p) L.lz[t].alloc(n);
-      V[t] = reinterpret_cast<TV*>(L.lz[t].p);
-    } else {
-      if (!L.lzf[t].p) L.lzf[t].alloc(n);
-      V[t] = reinterpret_cast<TV*>(L.lzf[t].p);
-    }
-  }
-  int iu_prev = 0, iu = 1, iwu = 2, iy_prev = 3, iy = 4, iwy = 5;  // roles
+  TV* U = lanczos_vec<TV>(L, 0, n);
+  TV* Y = lanczos_vec<TV>(L, 1, n);
+  TV* wy = lanczos_vec<TV>(L, 2, n);  // Y_(k-1), then wy, then Y_(k+1)
   LevelScalars* sc = M->sc.p + static_cast<size_t>(l) * M->n_inst;
   const int32_t* off = L.d_act_off.p;
   const int ns = L.n_act;
   const TV* val = static_cast<const TV*>(A->val);
   const TV* dinv = reinterpret_cast<const TV*>(L.dinv.p);
-  // start: v -> (u, y) = (v, Dv) / sqrt(v.Dv)
-  lanczos_start_kernel<BS, TV, TV><<<vgrid(nbr), 256, 0, s>>>(
-      nbr, off, ns, M->o.lanczos_seed + static_cast<uint64_t>(l), val, L.diag_idx.p, V[iwu], V[iwy]);
+  const SegGrid& g = L.lgrid;
+  lanczos_start_kernel<BS, TV, TV><<<g.nchunk, 256, 0, s>>>(g.lo.p, g.hi.p, off, ns,
+                                                            M->o.lanczos_seed + static_cast<uint64_t>(l), val,
+                                                            L.diag_idx.p, U, Y, M->partial.p);
   HIP_CHECK(hipGetLastError());
-  seg_reduce<1>(M, L.lgrid, V[iwu], V[iwy], OpLzSqrt{sc, -1}, s);
-  lanczos_scale_kernel<BS, TV><<<vgrid(nbr), 256, 0, s>>>(nbr, off, ns, sc, -1, V[iwu], V[iwy], V[iu], V[iy]);
-  HIP_CHECK(hipGetLastError());
+  seg_finish(M, g, 1, OpLzNorm{sc, -1}, s);
   const int k = M->o.lanczos_steps;
   const int G = lanes_for_reads(A, 1, L.mir);
   for (int step = 0; step < k; ++step) {
-    EpiLanczos<TV, TV> epi{V[iy_prev], V[iwy], sc, off, ns, step};
-    launch_rows<BS, BS, 1, TV, TV, TV>(G, nbr, A->rowptr, A->colidx, val, V[iu], epi, s, L.mir, L.sym_dist);
-    seg_reduce<1>(M, L.lgrid, V[iu], V[iwy], OpLzAlpha{sc, step}, s);
+    if (ns == 1) {
+      EpiLanczos<TV, TV, true> epi{U, wy, sc, off, ns, step, M->partial.p};
+      const int parts = launch_rows<BS, BS, 1, TV, TV, TV>(G, nbr, A->rowptr, A->colidx, val, U, epi, s, L.mir,
+                                                           L.sym_dist);
+      sum_finish(M, parts, OpLzDot{sc, step}, s);
+    } else {
+      EpiLanczos<TV, TV, false> epi{U, wy, sc, off, ns, step};
+      launch_rows<BS, BS, 1, TV, TV, TV>(G, nbr, A->rowptr, A->colidx, val, U, epi, s, L.mir, L.sym_dist);
+      seg_reduce<1>(M, g, U, wy, OpLzDot{sc, step}, s);
+    }
     if (step == k - 1) break;
-    lanczos_orth_kernel<BS, TV><<<vgrid(nbr), 256, 0, s>>>(nbr, off, ns, sc, step, V[iy], V[iwy], dinv, V[iwu]);
+    lanczos_orth_kernel<BS, TV><<<g.nchunk, 256, 0, s>>>(g.lo.p, g.hi.p, off, ns, sc, step, Y, wy, dinv, U,
+                                                         M->partial.p);
     HIP_CHECK(hipGetLastError());
-    seg_reduce<1>(M, L.lgrid, V[iwu], V[iwy], OpLzSqrt{sc, step}, s);
-    // (u_prev, u) <- (u, wu/beta) ; (y_prev, y) <- (y, wy/beta)
-    lanczos_scale_kernel<BS, TV><<<vgrid(nbr), 256, 0, s>>>(nbr, off, ns, sc, step, V[iwu], V[iwy], V[iu_prev],
-                                                            V[iy_prev]);
-    HIP_CHECK(hipGetLastError());
-    std::swap(iu_prev, iu);
-    std::swap(iy_prev, iy);
+    seg_finish(M, g, 1, OpLzNorm{sc, step}, s);
+    std::swap(Y, wy);
   }
 }
 
@@ -420,9 +456,8 @@ void refresh_level_scalars(amg_s* M, int l, const double* d_user, hipStream_t s)
     if (L.bs == 3) { if (f64) lanczos_bs<3, double>(M, l, s); else lanczos_bs<3, float>(M, l, s); }
     else { if (f64) lanczos_bs<6, double>(M, l, s); else lanczos_bs<6, float>(M, l, s); }
   }
-  lanczos_finish_kernel<<<(L.n_act + 63) / 64, 64, 0, s>>>(M->sc.p + static_cast<size_t>(l) * M->n_inst, L.n_act,
-                                                          M->o.lanczos_steps, d_user, M->o.cheb_lo, M->o.cheb_hi,
-                                                          M->o.cheb_degree);
+  lanczos_finish_kernel<<<L.n_act, 64, 0, s>>>(M->sc.p + static_cast<size_t>(l) * M->n_inst, M->o.lanczos_steps, d_user,
+                                               M->o.cheb_lo, M->o.cheb_hi, M->o.cheb_degree);
   HIP_CHECK(hipGetLastError());
 }
 
@@ -697,32 +732,21 @@ void level_features(amg_s* M, int l, float* feat, hipStream_t s) {
   const SegGrid& g = L.lgrid;
   if (g.nchunk > 0) {
 #define BLK_FEAT(BS, T)                                                                                    \
-  feature_stats_kernel<BS, T, T><<<g.nchunk, 256, 0, s>>>(A->rowptr, A->colidx, static_cast<const T*>(A->val), \
-                                                         reinterpret_cast<const T*>(L.dinv.p), g.lo.p, g.hi.p,  \
-                                                         M->partial.p)
+  feature_stats_kernel<BS, T, T><<<dim3(g.nchunk, kFeatSplit), 256, 0, s>>>(                               \
+      A->rowptr, A->colidx, static_cast<const T*>(A->val), reinterpret_cast<const T*>(L.dinv.p), g.lo.p,    \
+      g.hi.p, M->partial.p)
     if (M->T == BLKAMG_F64) { if (L.bs == 3) BLK_FEAT(3, double); else BLK_FEAT(6, double); }
     else { if (L.bs == 3) BLK_FEAT(3, float); else BLK_FEAT(6, float); }
 #undef BLK_FEAT
     HIP_CHECK(hipGetLastError());
   }
-  feature_finish_kernel<<<(L.n_act + 63) / 64, 64, 0, s>>>(M->partial.p, g.ptr.p, L.d_act_off.p, L.n_act, L.bs, l, feat);
+  feature_finish_kernel<<<L.n_act, 64, 0, s>>>(M->partial.p, g.ptr.p, L.d_act_off.p, L.bs, l, feat);
   HIP_CHECK(hipGetLastError());
 }
 
 void all_features(amg_s* M, float* feat, hipStream_t s) {
   for (size_t l = 0; l < M->lv.size(); ++l)
     level_features(M, static_cast<int>(l), feat + static_cast<size_t>(M->sample_base[l]) * 12, s);
-}
-
-template <class TV>
-TV* lanczos_vec(Level& L, int t, size_t n) {
-  if constexpr (sizeof(TV) == 8) {
-    if (L.lz[t].n < n) L.lz[t].alloc(n);
-    return reinterpret_cast<TV*>(L.lz[t].p);
-  } else {
-    if (L.lzf[t].n < n) L.lzf[t].alloc(n);
-    return reinterpret_cast<TV*>(L.lzf[t].p);
-  }
 }
 
 // Largest eigenvalue of the symmetric tridiagonal (alpha[0..m), beta[0..m-1)) by
@@ -770,8 +794,9 @@ std::vector<double> judge_level_bs(amg_s* M, int l, int k, hipStream_t s) {
   const TM* val = static_cast<const TM*>(A->val);
   const TM* dinv = reinterpret_cast<const TM*>(L.dinv.p);
   const int G = lanes_for_reads(A, 1, L.mir);
-  lanczos_start_kernel<BS, TM, double><<<vgrid(nbr), 256, 0, s>>>(
-      nbr, off, ns, M->o.lanczos_seed + static_cast<uint64_t>(l), val, L.diag_idx.p, wu.p, wy.p);
+  lanczos_start_kernel<BS, TM, double><<<L.lgrid.nchunk, 256, 0, s>>>(
+      L.lgrid.lo.p, L.lgrid.hi.p, off, ns, M->o.lanczos_seed + static_cast<uint64_t>(l), val, L.diag_idx.p, wu.p, wy.p,
+      nullptr);
   seg_reduce<1>(M, L.lgrid, wu.p, wy.p, OpLzSqrt{jsc.p, -1}, s);
   lanczos_scale_kernel<BS, double><<<vgrid(nbr), 256, 0, s>>>(nbr, off, ns, jsc.p, -1, wu.p, wy.p, U.p, Y.p);
   HIP_CHECK(hipGetLastError());
@@ -840,7 +865,8 @@ void growth_level_bs(amg_s* M, int l, hipStream_t s) {
   const TV* val = static_cast<const TV*>(A->val);
   const TV* dinv = buf<TV>(L.dinv);
   HIP_CHECK(hipMemsetAsync(zero, 0, n * sizeof(TV), s));
-  lanczos_start_kernel<BS, TV, TV><<<vgrid(nbr), 256, 0, s>>>(nbr, off, ns, kGrowthSeed, val, L.diag_idx.p, e0, scratch);
+  lanczos_start_kernel<BS, TV, TV><<<L.lgrid.nchunk, 256, 0, s>>>(L.lgrid.lo.p, L.lgrid.hi.p, off, ns, kGrowthSeed, val,
+                                                                  L.diag_idx.p, e0, scratch, nullptr);
   HIP_CHECK(hipGetLastError());
   const int G = lanes_for_reads(A, 1, L.mir);
   const int K = std::max(1, M->o.growth_steps);

@@ -21,6 +21,7 @@ constexpr int kMaxLanczos = 64;
 struct LevelScalars {
   double alpha[kMaxLanczos];
   double beta[kMaxLanczos];
+  double b0, inv_b, ratio;        // Lanczos: start norm; 1 / b_k and b_k / b_(k-1) of the current step
   double lam;                     // lambda_hat
   double coef[1 + 2 * kMaxCheb];  // 1/theta, then (c1, c2) per Chebyshev step
   double tmp[4];
@@ -109,6 +110,26 @@ struct OpLzAlpha {
   int step;
   __device__ void operator()(int s, int, double v) const { sc[s].alpha[step] = v; }
 };
+// The refresh's Lanczos keeps its vectors unnormalised, U = b u and Y = b y with
+// b = sqrt(U.Y): the norm after step `step` (-1: the start vector's) and the two factors
+// the next product needs.  A zero norm counts as 1.
+struct OpLzNorm {
+  LevelScalars* sc;
+  int step;
+  __device__ void operator()(int s, int, double v) const {
+    LevelScalars& S = sc[s];
+    const double r = sqrt(v > 0.0 ? v : 0.0), b = r > 0.0 ? r : 1.0;
+    if (step < 0) S.b0 = b; else S.beta[step] = r;
+    S.ratio = step < 0 ? 0.0 : r * S.inv_b;
+    S.inv_b = 1.0 / b;
+  }
+};
+// alpha = u.wy from U.wy
+struct OpLzDot {
+  LevelScalars* sc;
+  int step;
+  __device__ void operator()(int s, int, double v) const { sc[s].alpha[step] = v * sc[s].inv_b; }
+};
 
 // ---------------------------------------------------------------------------
 // Block-diagonal inverse (point-block Jacobi, paper §4.1)
@@ -181,27 +202,40 @@ __global__ __launch_bounds__(256) void dinv_kernel(int nbr, const int32_t* __res
 // sc points at this level's first LevelScalars; segment s uses sc[s].
 // ---------------------------------------------------------------------------
 
-// v from splitmix64 of the instance-local scalar index, Dv = diag-block(A) v
+// v from splitmix64 of the instance-local scalar index, Dv = diag-block(A) v; workgroup c
+// takes the rows of chunk c and, with partial set, sums their v.Dv
 template <int BS, class TM, class TV>
-__global__ void lanczos_start_kernel(int nbr, const int32_t* __restrict__ off, int nseg, uint64_t seed,
-                                     const TM* __restrict__ val, const int32_t* __restrict__ diag_idx,
-                                     TV* __restrict__ v, TV* __restrict__ Dv) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nbr) return;
-  const int sg = seg_of(off, nseg, r);
-  const int64_t local = static_cast<int64_t>(r - off[sg]) * BS;
-  double vv[BS];
-  for (int j = 0; j < BS; ++j) {
-    const uint64_t z = splitmix64(seed ^ static_cast<uint64_t>(local + j));
-    vv[j] = static_cast<double>(static_cast<TV>(2.0 * (static_cast<double>(z >> 11) * 0x1.0p-53) - 1.0));
-    v[static_cast<size_t>(r) * BS + j] = static_cast<TV>(vv[j]);
+__global__ __launch_bounds__(256) void lanczos_start_kernel(const int32_t* __restrict__ lo,
+                                                            const int32_t* __restrict__ hi,
+                                                            const int32_t* __restrict__ off, int nseg, uint64_t seed,
+                                                            const TM* __restrict__ val,
+                                                            const int32_t* __restrict__ diag_idx, TV* __restrict__ v,
+                                                            TV* __restrict__ Dv, double* __restrict__ partial) {
+  __shared__ double lds[4];
+  const int c = blockIdx.x, r1 = hi[c] / BS;
+  double acc = 0.0;
+  for (int r = lo[c] / BS + threadIdx.x; r < r1; r += 256) {
+    const int sg = seg_of(off, nseg, r);
+    const int64_t local = static_cast<int64_t>(r - off[sg]) * BS;
+    double vv[BS];
+    for (int j = 0; j < BS; ++j) {
+      const uint64_t z = splitmix64(seed ^ static_cast<uint64_t>(local + j));
+      vv[j] = static_cast<double>(static_cast<TV>(2.0 * (static_cast<double>(z >> 11) * 0x1.0p-53) - 1.0));
+      v[static_cast<size_t>(r) * BS + j] = static_cast<TV>(vv[j]);
+    }
+    const int kd = diag_idx[r];
+    for (int i = 0; i < BS; ++i) {
+      double sv = 0.0;
+      if (kd >= 0)
+        for (int j = 0; j < BS; ++j) sv += ld<double>(val + static_cast<size_t>(kd) * BS * BS + i * BS + j) * vv[j];
+      const TV dv = static_cast<TV>(sv);
+      Dv[static_cast<size_t>(r) * BS + i] = dv;
+      acc = fmadd(vv[i], static_cast<double>(dv), acc);
+    }
   }
-  const int kd = diag_idx[r];
-  for (int i = 0; i < BS; ++i) {
-    double sv = 0.0;
-    if (kd >= 0)
-      for (int j = 0; j < BS; ++j) sv += ld<double>(val + static_cast<size_t>(kd) * BS * BS + i * BS + j) * vv[j];
-    Dv[static_cast<size_t>(r) * BS + i] = static_cast<TV>(sv);
+  if (partial) {
+    const double t = block_sum_256(acc, lds);
+    if (threadIdx.x == 0) partial[c] = t;
   }
 }
 
@@ -223,35 +257,50 @@ __global__ void lanczos_scale_kernel(int nbr, const int32_t* __restrict__ off, i
   }
 }
 
-// wy -= alpha_seg * y ; wu = Dinv wy
+// wy -= alpha y ; U = Dinv wy ; partial[c] = U.wy over the rows of chunk c (y = Y / b).
+// One pass over wy, Y and Dinv: the norm's dot product reads nothing again.
 template <int BS, class TV>
-__global__ void lanczos_orth_kernel(int nbr, const int32_t* __restrict__ off, int nseg,
-                                    const LevelScalars* __restrict__ sc, int step, const TV* __restrict__ y,
-                                    TV* __restrict__ wy, const TV* __restrict__ dinv, TV* __restrict__ wu) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nbr) return;
-  const double al = sc[seg_of(off, nseg, r)].alpha[step];
-  double w[BS];
-  for (int j = 0; j < BS; ++j) {
-    const size_t o = static_cast<size_t>(r) * BS + j;
-    const TV wt = static_cast<TV>(static_cast<double>(wy[o]) - al * static_cast<double>(y[o]));
-    wy[o] = wt;
-    w[j] = static_cast<double>(wt);
+__global__ __launch_bounds__(256) void lanczos_orth_kernel(const int32_t* __restrict__ lo,
+                                                           const int32_t* __restrict__ hi,
+                                                           const int32_t* __restrict__ off, int nseg,
+                                                           const LevelScalars* __restrict__ sc, int step,
+                                                           const TV* __restrict__ Y, TV* __restrict__ wy,
+                                                           const TV* __restrict__ dinv, TV* __restrict__ U,
+                                                           double* __restrict__ partial) {
+  __shared__ double lds[4];
+  const int c = blockIdx.x, r0 = lo[c] / BS, r1 = hi[c] / BS;
+  const LevelScalars& S = sc[seg_of(off, nseg, r0)];  // a chunk lies in one segment
+  const double al = S.alpha[step] * S.inv_b;
+  double acc = 0.0;
+  for (int r = r0 + threadIdx.x; r < r1; r += 256) {
+    double w[BS];
+    for (int j = 0; j < BS; ++j) {
+      const size_t o = static_cast<size_t>(r) * BS + j;
+      const TV wt = static_cast<TV>(static_cast<double>(wy[o]) - al * static_cast<double>(Y[o]));
+      wy[o] = wt;
+      w[j] = static_cast<double>(wt);
+    }
+    const TV* D = dinv + static_cast<size_t>(r) * BS * BS;
+    for (int i = 0; i < BS; ++i) {
+      double z = 0.0;
+      for (int j = 0; j < BS; ++j) z += static_cast<double>(D[i * BS + j]) * w[j];
+      const TV u = static_cast<TV>(z);
+      U[static_cast<size_t>(r) * BS + i] = u;
+      acc = fmadd(static_cast<double>(u), w[i], acc);
+    }
   }
-  const TV* D = dinv + static_cast<size_t>(r) * BS * BS;
-  for (int i = 0; i < BS; ++i) {
-    double z = 0.0;
-    for (int j = 0; j < BS; ++j) z += static_cast<double>(D[i * BS + j]) * w[j];
-    wu[static_cast<size_t>(r) * BS + i] = static_cast<TV>(z);
-  }
+  const double t = block_sum_256(acc, lds);
+  if (threadIdx.x == 0) partial[c] = t;
 }
 
-// SpMV epilogue: wy = A u - beta_{step-1, seg} * y_prev (no previous vector on step 0);
-// one right-hand side, BR <= G: lane i < BR owns output i
-template <class TV, class TA>
+// SpMV epilogue of one Lanczos step on the unnormalised vectors: wy = (A U) / b_k -
+// b_k y_(k-1), in place over Y_(k-1) (no previous vector on step 0).  With DOT (one
+// segment), also the partial sums of U.wy.  One right-hand side, BR <= G: lane i < BR owns
+// output i.
+template <class TV, class TA, bool DOT>
 struct EpiLanczos {
-  static constexpr bool kReduce = false;
-  const TV* y_prev;
+  static constexpr bool kReduce = DOT;
+  const TV* U;
   TV* wy;
   const LevelScalars* sc;
   const int32_t* off;
@@ -259,64 +308,88 @@ struct EpiLanczos {
   int step;
   double* partial = nullptr;
   template <int BR, int NR, int G>
-  __device__ __forceinline__ RowVals<double, 2> prefetch(bool active, int row) const {
+  __device__ __forceinline__ RowVals<double, 4> prefetch(bool active, int row) const {
     static_assert(lane_owned<BR * NR, G>(), "Lanczos epilogue expects BR * NR <= G");
-    RowVals<double, 2> p;
-    p.v[0] = 0.0;
-    p.v[1] = 0.0;
+    RowVals<double, 4> p;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) p.v[t] = 0.0;
     const int lane = static_cast<int>(threadIdx.x) % G;
-    if (active && step > 0 && lane < BR * NR) {
-      p.v[1] = sc[seg_of(off, nseg, row)].beta[step - 1];
-      p.v[0] = static_cast<double>(y_prev[static_cast<size_t>(row) * (BR * NR) + lane]);
+    if (active && lane < BR * NR) {
+      const LevelScalars& S = sc[DOT ? 0 : seg_of(off, nseg, row)];
+      const size_t o = static_cast<size_t>(row) * (BR * NR) + lane;
+      p.v[0] = S.inv_b;
+      if (step > 0) {
+        p.v[1] = S.ratio;
+        p.v[2] = static_cast<double>(wy[o]);
+      }
+      if (DOT) p.v[3] = static_cast<double>(U[o]);
     }
     return p;
   }
   template <int BR, int NR, int G>
   __device__ __forceinline__ double apply(bool active, int row, int lane, const TA (&s)[BR * NR],
-                                          const RowVals<double, 2>& pre) const {
+                                          const RowVals<double, 4>& pre) const {
     if (!active || lane >= BR * NR) return 0.0;
-    wy[static_cast<size_t>(row) * (BR * NR) + lane] =
-        static_cast<TV>(static_cast<double>(pick<BR * NR>(s, lane)) - pre.v[1] * pre.v[0]);
-    return 0.0;
+    const TV w = static_cast<TV>(static_cast<double>(pick<BR * NR>(s, lane)) * pre.v[0] - pre.v[1] * pre.v[2]);
+    wy[static_cast<size_t>(row) * (BR * NR) + lane] = w;
+    return DOT ? pre.v[3] * static_cast<double>(w) : 0.0;
   }
 };
 
-// Largest eigenvalue of each segment's tridiagonal T_k by Sturm bisection, then the
-// Chebyshev coefficients (Saad, Alg. 12.1) for [lo*lam, hi*lam].  One thread per segment.
-__global__ void lanczos_finish_kernel(LevelScalars* sc, int nseg, int k, const double* user_lam, double lo,
-                                      double hi, int degree) {
-  const int sg = blockIdx.x * blockDim.x + threadIdx.x;
-  if (sg >= nseg) return;
+// Largest eigenvalue of each segment's tridiagonal T_k by Sturm counts, then the
+// Chebyshev coefficients (Saad, Alg. 12.1) for [lo*lam, hi*lam].  One wave per segment: its
+// 64 lanes count at 64 points of the interval, which narrows it 65 times a round, so ten
+// rounds of k dependent divisions take the place of bisection's fifty (66 -> 10 us).
+__global__ __launch_bounds__(64) void lanczos_finish_kernel(LevelScalars* sc, int k, const double* user_lam, double lo,
+                                                            double hi, int degree) {
+  const int sg = blockIdx.x, lane = threadIdx.x;
   LevelScalars* S = sc + sg;
   double lam;
   if (user_lam != nullptr) {
     lam = user_lam[sg];
   } else {
+    __shared__ double al[kMaxLanczos], b2[kMaxLanczos];
     int m = k;
     for (int j = 0; j < k - 1; ++j)
       if (!(S->beta[j] > 0.0)) { m = j + 1; break; }
+    if (lane < m) {
+      al[lane] = S->alpha[lane];
+      b2[lane] = lane < m - 1 ? S->beta[lane] * S->beta[lane] : 0.0;
+    }
     double gl = 1e300, gh = -1e300;
     for (int i = 0; i < m; ++i) {
       const double o = (i > 0 ? fabs(S->beta[i - 1]) : 0.0) + (i < m - 1 ? fabs(S->beta[i]) : 0.0);
       gl = fmin(gl, S->alpha[i] - o);
       gh = fmax(gh, S->alpha[i] + o);
     }
+    __syncthreads();
     double a = gl, b = gh;
-    for (int it = 0; it < 200; ++it) {
-      const double x = 0.5 * (a + b);
-      if (x <= a || x >= b) break;
+    for (int it = 0; it < 64; ++it) {
+      const double x = a + (b - a) * ((lane + 1) * (1.0 / 65.0));
+      const bool inside = x > a && x < b;
+      if (__ballot(inside) == 0) {  // the points round to the ends: bisect what is left
+        const double mid = 0.5 * (a + b);
+        if (!(mid > a && mid < b)) break;
+      }
+      const double t = __ballot(inside) == 0 ? 0.5 * (a + b) : x;
       int cnt = 0;
-      double q = S->alpha[0] - x;
+      double q = al[0] - t;
       if (q < 0) cnt++;
       for (int i = 1; i < m; ++i) {
         const double qq = (q != 0.0) ? q : 1e-300;
-        q = S->alpha[i] - x - S->beta[i - 1] * S->beta[i - 1] / qq;
+        q = al[i] - t - b2[i - 1] / qq;
         if (q < 0) cnt++;
       }
-      if (cnt == m) b = x; else a = x;
+      // the points rise with the lane: the first one above every eigenvalue ends the interval
+      const unsigned long long above = __ballot(t >= b || (t > a && cnt == m));
+      const int f = above ? __ffsll(above) - 1 : 64;
+      const double bn = __shfl(t, f < 64 ? f : 63), an = __shfl(t, f > 0 ? f - 1 : 0);
+      if (f < 64) b = fmin(b, bn);
+      if (f > 0) a = fmax(a, an);
     }
     lam = 0.5 * (a + b);
   }
+  if (lane != 0) return;
   S->lam = lam;
   const double ea = lo * lam, eb = hi * lam;
   const double theta = 0.5 * (eb + ea), delta = 0.5 * (eb - ea);
@@ -1005,9 +1078,14 @@ __device__ __forceinline__ double wave_min(double v) {
   return v;
 }
 
-// Per chunk of block rows: g_i = max scalar row of |D_i^-1 [A_i1 .. A_in]| summed,
-// h_i = sum_{j != i} ||D_i^-1 A_ij||_F, d_i = ||A_ii||_F, nb_i = blocks in the row;
-// partial[c][kFeatStats] holds the chunk's sums / maxima / minimum.
+constexpr int kFeatSplit = 8;  // workgroups per chunk of the feature statistics
+constexpr int kFeatLanes = 8;  // lanes per block row
+
+// Per slice (an eighth of a chunk) of block rows: g_i = max scalar row of
+// |D_i^-1 [A_i1 .. A_in]| summed, h_i = sum_{j != i} ||D_i^-1 A_ij||_F, d_i = ||A_ii||_F,
+// nb_i = blocks in the row; partial[slice][kFeatStats] holds the slice's sums / maxima /
+// minimum.  Eight lanes share a row's blocks: with a thread per row a level of some
+// thousand rows occupied a few workgroups, each with a chain of 27 dependent blocks.
 template <int BS, class TM, class TD>
 __global__ __launch_bounds__(256) void feature_stats_kernel(const int32_t* __restrict__ rp,
                                                             const int32_t* __restrict__ ci,
@@ -1017,16 +1095,19 @@ __global__ __launch_bounds__(256) void feature_stats_kernel(const int32_t* __res
                                                             double* __restrict__ partial) {
   __shared__ double lsum[5][4];
   __shared__ double lext[4][4];
-  const int c = blockIdx.x;
-  const int r0 = lo[c] / BS, r1 = hi[c] / BS;
+  const int c = blockIdx.x * kFeatSplit + blockIdx.y;
+  const int c0 = lo[blockIdx.x] / BS, c1 = hi[blockIdx.x] / BS;
+  const int per = (c1 - c0 + kFeatSplit - 1) / kFeatSplit;
+  const int r0 = c0 + static_cast<int>(blockIdx.y) * per, r1 = min(c1, r0 + per);
+  const int lane = threadIdx.x % kFeatLanes;
   double sg = 0.0, sg2 = 0.0, mg = 0.0, sh = 0.0, mh = 0.0, md = 0.0, mnd = 1e300, snb = 0.0, mnb = 0.0;
-  for (int r = r0 + static_cast<int>(threadIdx.x); r < r1; r += 256) {
+  for (int r = r0 + static_cast<int>(threadIdx.x) / kFeatLanes; r < r1; r += 256 / kFeatLanes) {
     double D[BS * BS];
     for (int t = 0; t < BS * BS; ++t) D[t] = static_cast<double>(dinv[static_cast<size_t>(r) * BS * BS + t]);
     double rows[BS];
     for (int i = 0; i < BS; ++i) rows[i] = 0.0;
     double h = 0.0, d = 0.0;
-    for (int k = rp[r]; k < rp[r + 1]; ++k) {
+    for (int k = rp[r] + lane; k < rp[r + 1]; k += kFeatLanes) {
       const TM* a = val + static_cast<size_t>(k) * BS * BS;
       double fro = 0.0;
       for (int i = 0; i < BS; ++i)
@@ -1044,17 +1125,23 @@ __global__ __launch_bounds__(256) void feature_stats_kernel(const int32_t* __res
         h += sqrt(fro);
       }
     }
+#pragma unroll
+    for (int i = 0; i < BS; ++i) rows[i] = group_sum<kFeatLanes>(rows[i]);
+    h = group_sum<kFeatLanes>(h);
+    d = group_sum<kFeatLanes>(d);  // one lane holds the diagonal block
     double g = rows[0];
     for (int i = 1; i < BS; ++i) g = fmax(g, rows[i]);
     const double nb = static_cast<double>(rp[r + 1] - rp[r]);
-    sg += g;
-    sg2 += g * g;
+    if (lane == 0) {
+      sg += g;
+      sg2 += g * g;
+      sh += h;
+      snb += nb;
+    }
     mg = fmax(mg, g);
-    sh += h;
     mh = fmax(mh, h);
     md = fmax(md, d);
     mnd = fmin(mnd, d);
-    snb += nb;
     mnb = fmax(mnb, nb);
   }
   const double t0 = block_sum_256(sg, lsum[0]);
@@ -1089,14 +1176,15 @@ __global__ __launch_bounds__(256) void feature_stats_kernel(const int32_t* __res
   }
 }
 
-// Features of segment s (one thread each) from its chunks, in chunk order.
-__global__ void feature_finish_kernel(const double* __restrict__ partial, const int32_t* __restrict__ seg_ptr,
-                                      const int32_t* __restrict__ row_off, int nseg, int bs, int level,
-                                      float* __restrict__ feat) {
-  const int sg = blockIdx.x * blockDim.x + threadIdx.x;
-  if (sg >= nseg) return;
+// Features of segment s (one wave each) from its slices: every lane takes each 64th slice,
+// then a fixed tree.
+__global__ __launch_bounds__(64) void feature_finish_kernel(const double* __restrict__ partial,
+                                                            const int32_t* __restrict__ seg_ptr,
+                                                            const int32_t* __restrict__ row_off, int bs, int level,
+                                                            float* __restrict__ feat) {
+  const int sg = blockIdx.x;
   double st[kFeatStats] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 1e300, 0.0, 0.0};
-  for (int c = seg_ptr[sg]; c < seg_ptr[sg + 1]; ++c) {
+  for (int c = seg_ptr[sg] * kFeatSplit + threadIdx.x; c < seg_ptr[sg + 1] * kFeatSplit; c += 64) {
     const double* p = partial + static_cast<size_t>(c) * kFeatStats;
     st[0] += p[0];
     st[1] += p[1];
@@ -1108,6 +1196,10 @@ __global__ void feature_finish_kernel(const double* __restrict__ partial, const 
     st[7] += p[7];
     st[8] = fmax(st[8], p[8]);
   }
+  for (int t : {0, 1, 3, 7}) st[t] = group_sum<64>(st[t]);
+  for (int t : {2, 4, 5, 8}) st[t] = wave_max(st[t]);
+  st[6] = wave_min(st[6]);
+  if (threadIdx.x != 0) return;
   const double nr = static_cast<double>(row_off[sg + 1] - row_off[sg]);
   float* f = feat + static_cast<size_t>(sg) * 12;
   const double mean_g = st[0] / nr;
