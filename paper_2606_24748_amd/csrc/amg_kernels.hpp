@@ -437,8 +437,8 @@ enum SmoothMode { M_RESID = 0, M_INITX = 1, M_STEP = 2 };
 // One right-hand side: lane i < BR owns output i; it loads f_i, d_i, x_i, row i of
 // Dinv and the two coefficients before the product (their latency then hides behind
 // the block loads), and the residual entries reach the other owners by shuffles.
-// Eight right-hand sides: lane q < 8 owns column q of the row (all BR entries), so
-// D^-1 r stays inside the lane; its operands are loaded after the product.
+// Eight right-hand sides: a lane holds its columns of all BR entries, so D^-1 r stays
+// inside the lane; its operands are loaded after the product.
 template <int MODE, class TV, class TA>
 struct EpiSmooth {
   static constexpr bool kReduce = false;
@@ -524,33 +524,48 @@ struct EpiSmooth {
     return 0.0;
   }
 
-  template <int BR, int G>
-  __device__ __forceinline__ void apply8(bool active, int row, int lane, const TA (&s)[BR]) const {
-    if (!active || lane >= 8) return;
-    const size_t base = static_cast<size_t>(row) * (BR * 8) + lane;
-    TA r[BR];
+  // eight right-hand sides: every lane holds its CPL columns of the row's BR sums and
+  // forms the residual of all of them; slot `slot` finishes rows slot, slot + S, ...
+  template <int BR, int S, int CPL>
+  __device__ __forceinline__ void apply8(int row, int slot, int cl, const TA (&s)[BR][CPL]) const {
+    const size_t base = static_cast<size_t>(row) * (BR * 8) + cl * CPL;
+    TA r[BR][CPL];
 #pragma unroll
-    for (int i = 0; i < BR; ++i) r[i] = ld<TA>(f + base + i * 8) - s[i];
-    if (MODE == M_RESID) {
+    for (int i = 0; i < BR; ++i) {
+      if (MODE == M_RESID && i % S != slot) continue;
+      TA fv[CPL];
+      ld_cols<TA>(f + base + i * 8, fv);
 #pragma unroll
-      for (int i = 0; i < BR; ++i) r_out[base + i * 8] = static_cast<TV>(r[i]);
-      return;
+      for (int q = 0; q < CPL; ++q) r[i][q] = fv[q] - s[i][q];
+      if (MODE == M_RESID) st_cols(r_out + base + i * 8, r[i]);
     }
-    const LevelScalars& S = scal(row);
-    const TA c1 = MODE == M_STEP ? cheb_coef<TA>(S, 1 + 2 * step) : TA(0);
-    const TA c2 = MODE == M_STEP ? cheb_coef<TA>(S, 2 + 2 * step) : cheb_coef<TA>(S, 0);
+    if (MODE == M_RESID) return;
+    // r_out may be f: every lane of the row has read f before any of them stores
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const LevelScalars& L = scal(row);
+    const TA c1 = MODE == M_STEP ? cheb_coef<TA>(L, 1 + 2 * step) : TA(0);
+    const TA c2 = MODE == M_STEP ? cheb_coef<TA>(L, 2 + 2 * step) : cheb_coef<TA>(L, 0);
     const TV* D = dinv + static_cast<size_t>(row) * (BR * BR);
 #pragma unroll
     for (int i = 0; i < BR; ++i) {
-      TA z = TA(0);
-#pragma unroll
-      for (int j = 0; j < BR; ++j) z = fmadd(ld<TA>(D + i * BR + j), r[j], z);
+      if (i % S != slot) continue;
       const size_t o = base + i * 8;
-      TA dn = c2 * z;
-      if (MODE == M_STEP) dn = fmadd(c1, ld<TA>(d_in + o), dn);
-      x_out[o] = static_cast<TV>(ld<TA>(x_in + o) + dn);
-      if (r_out) r_out[o] = static_cast<TV>(r[i]);
-      if (d_out) d_out[o] = static_cast<TV>(dn);
+      TA xi[CPL], di[CPL], dn[CPL];
+      ld_cols<TA>(x_in + o, xi);
+      if (MODE == M_STEP) ld_cols<TA>(d_in + o, di);
+#pragma unroll
+      for (int q = 0; q < CPL; ++q) {
+        TA z = TA(0);
+#pragma unroll
+        for (int j = 0; j < BR; ++j) z = fmadd(ld<TA>(D + i * BR + j), r[j][q], z);
+        dn[q] = c2 * z;
+        if (MODE == M_STEP) dn[q] = fmadd(c1, di[q], dn[q]);
+        xi[q] += dn[q];
+      }
+      st_cols(x_out + o, xi);
+      if (r_out) st_cols(r_out + o, r[i]);
+      if (d_out) st_cols(d_out + o, dn);
     }
   }
 };

@@ -96,6 +96,20 @@ int lanes_for(const bsr_s* A, int nrhs) {
   if (const int t = A->tuned[nrhs > 1 ? 1 : 0]) return t;
   const double avg = A->avg_blocks_per_row();
   const size_t vb = A->block_elems() * dtype_size(A->dtype);  // bytes per block
+  if (nrhs > 1) {
+    // Eight right-hand sides, measured at 64^3 nodes (FP64 / FP32, us).  Few blocks per row
+    // (prolongators, 4.5): 8 x 1 42 / 25 against 48 / 34 with 16 x 1.  27 per row: 16 x 2,
+    // 162 / 84 against 193 / 91 with 8 lanes and 171 / 93 with 32 x 2 (6x6: 20 / 14 against
+    // 23-30 / 14-18).  Long rows of 3x3 blocks (triquadratic, 62 per row): 64 x 1 in FP64
+    // (164 against 175 with 32 x 1), 32 x 1 in FP32 (90 against 101).  Restrictions (106-121):
+    // 64 x 2, 43 / 28 against 46 / 26 with 16 x 2 there but 33 / 22 against 102 / 56 where
+    // there are few rows.
+    if (avg <= 8.0) return lane_code(8, 1);
+    if (avg <= 16.0) return lane_code(16, 1);
+    if (avg <= 40.0) return lane_code(16, 2);
+    if (A->block_elems() >= 18) return lane_code(64, 2);
+    return A->dtype == BLKAMG_F64 ? lane_code(64, 1) : lane_code(32, 1);
+  }
   // Measured on the 128^3 hierarchy.  Fine 3x3 operator (27 blocks per row): 32 lanes,
   // one block per lane, for both F32 and F64.  6x6 F64 blocks (288 bytes) want two
   // blocks per lane and fewer lanes (level-1 operator, 26 per row: 16 x 2 112 us against
