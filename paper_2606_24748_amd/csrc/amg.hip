@@ -1187,10 +1187,10 @@ std::unique_ptr<amg_s> new_amg(const blkamg_opts& o, bsr_s* A0, int32_t n_inst, 
   M->n_inst = n_inst;
   M->inst_row0 = row0;
   M->flags.alloc(4);
-  HIP_CHECK(hipMemset(M->flags.p, 0, 4 * sizeof(int)));
+  zero_now(M->flags.p, 4 * sizeof(int));
   const size_t nsc = static_cast<size_t>(o.max_levels) * n_inst;
   M->sc.alloc(nsc);
-  HIP_CHECK(hipMemset(M->sc.p, 0, nsc * sizeof(LevelScalars)));
+  zero_now(M->sc.p, nsc * sizeof(LevelScalars));
   M->partial.alloc(static_cast<size_t>(A0->nbr) / 4 + 8192);
   M->partial2.alloc(256);
   M->pcg_s.alloc(S_COUNT);
@@ -1252,6 +1252,7 @@ amg_s* setup_impl(bsr_t A0, int32_t n_inst, const int32_t* h_row0, const double*
   for (int t = 0; t < n_inst; ++t) BLK_REQUIRE(row0[t + 1] > row0[t], BLKAMG_EINVAL, "empty instance");
   hipStream_t s = as_stream(stream);
   HIP_CHECK(hipStreamSynchronize(s));
+  AllocScope scope;
   if (n_inst > 1) check_block_diagonal(A0, row0);
 
   auto M = new_amg(o, A0, n_inst, row0);

@@ -41,7 +41,7 @@ std::unique_ptr<bsr_s> make_owned(int32_t nbr, int32_t nbc, int32_t br, int32_t 
   upload(A->own_rowptr, h_rowptr);
   upload(A->own_colidx, h_colidx);
   A->own_val.alloc(std::max<size_t>(A->val_bytes(), 0));
-  if (A->own_val.p) HIP_CHECK(hipMemset(A->own_val.p, 0, A->val_bytes()));
+  if (A->own_val.p) zero_now(A->own_val.p, A->val_bytes());
   A->rowptr = A->own_rowptr.p;
   A->colidx = A->own_colidx.p;
   A->val = A->own_val.p;

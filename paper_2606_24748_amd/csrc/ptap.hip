@@ -731,6 +731,7 @@ int ptap_symbolic_ex(bsr_t A, bsr_t P, int flags, bsr_t* C, void* stream) {
               BLKAMG_EINVAL, "dtype combination must be F64/F64, F32/F32 or F32/BF16");
   hipStream_t s = as_stream(stream);
   HIP_CHECK(hipStreamSynchronize(s));
+  AllocScope scope;
   const char* tune = std::getenv("BLKAMG_PTAP_TUNE");
   const PtapTune tn{tune ? tune : "ap_sort"};
   const bool search = std::getenv("BLKAMG_PTAP_SEARCH") != nullptr;
