@@ -64,7 +64,8 @@ PTAP_TRAFFIC_RECORD = {
     "fetch_bytes": 34558126080,  # FETCH_SIZE 16,874,085 KiB x 2.00
     "write_bytes": 5251006464,   # WRITE_SIZE 5,127,936 KiB x 1.00
 }
-PTAP_TRAFFIC_SOURCES = ("paper_2606_24748_amd/csrc/ptap.hip", "paper_2606_24748_amd/csrc/ptap_plan.hpp",
+PTAP_TRAFFIC_SOURCES = ("paper_2606_24748_amd/csrc/ptap.hip", "paper_2606_24748_amd/csrc/ptap_brick.hip",
+                        "paper_2606_24748_amd/csrc/ptap_plan.hpp",
                         "paper_2606_24748_amd/csrc/ptap_symbolic.hip", "paper_2606_24748_amd/csrc/common.hpp")
 
 

@@ -517,7 +517,8 @@ const bsr_s* ap_for(amg_s* M, int l) {
     return nullptr;
   if (L.ap_stamp != L.A->stamp || L.ap_pstamp != L.P->stamp) return nullptr;
   const auto* pl = static_cast<const PtapPlan*>(M->lv[l + 1]->A->ext.get());
-  if (!pl || pl->A != L.A_act.get() || pl->P != L.P.get() || pl->n_ap_rows != L.act_rows || pl->ap_nslots <= 0)
+  if (!pl || pl->A != L.A_act.get() || pl->P != L.P.get() || pl->n_ap_rows != L.act_rows || pl->ap_nslots <= 0 ||
+      !pl->ap_val.p)
     return nullptr;
   const double vs = static_cast<double>(dtype_size(M->T));
   const double ap_bytes = static_cast<double>(pl->ap_nslots) * (L.bs * L.P->bc * vs + 4.0);
@@ -1390,7 +1391,10 @@ amg_s* setup_impl(bsr_t A0, int32_t n_inst, const int32_t* h_row0, const double*
       HIP_CHECK(hipStreamSynchronize(s));  // dom (and dagg / dpt below) are freed at scope exit
     }
     bsr_t Cm = nullptr;
-    int rc = ptap_symbolic_ex(A, L.P.get(), BLKAMG_PTAP_SYMMETRIC, &Cm, stream);
+    // an F32 hierarchy makes its own plans below; the F64 levels read A P only where
+    // symmetric reads of A are off
+    int rc = ptap_symbolic_for(A, L.P.get(), BLKAMG_PTAP_SYMMETRIC, o.hier_dtype == BLKAMG_F32,
+                               o.ap_residual && !o.sym_spmv, &Cm, stream);
     if (rc != BLKAMG_OK) fail(rc, std::string("ptap_symbolic: ") + blkamg_last_error());
     next->A_own.reset(Cm);
     next->A = Cm;
@@ -1420,7 +1424,8 @@ amg_s* setup_impl(bsr_t A0, int32_t n_inst, const int32_t* h_row0, const double*
         std::unique_ptr<bsr_s> Pf = clone_pattern(P64, o.p_dtype);
         cast_values(P64->val, BLKAMG_F64, Pf->val, o.p_dtype, static_cast<size_t>(P64->nnzb) * P64->block_elems(), s);
         bsr_t Cm = nullptr;
-        int rc = ptap_symbolic_ex(L.A_act.get(), Pf.get(), BLKAMG_PTAP_SYMMETRIC, &Cm, stream);
+        int rc = ptap_symbolic_for(L.A_act.get(), Pf.get(), BLKAMG_PTAP_SYMMETRIC, false, o.ap_residual != 0, &Cm,
+                                   stream);
         if (rc != BLKAMG_OK) fail(rc, std::string("ptap_symbolic: ") + blkamg_last_error());
         Af.reset(Cm);
         rc = ptap_numeric(L.A_act.get(), Pf.get(), Cm, stream);

@@ -498,6 +498,24 @@ void run_numeric(const PtapPlan& pl, const bsr_s* A, const bsr_s* P, const bsr_s
   }
 }
 
+// Bytes of reading A P against those of reading A, with an index per block each.
+bool ap_cheaper(const PtapPlan& pl, const bsr_s* A, const bsr_s* P) {
+  const double vs = A->dtype == BLKAMG_F64 ? 8.0 : 4.0;
+  return static_cast<double>(pl.ap_nslots) * (A->br * P->bc * vs + 4.0) <
+         static_cast<double>(A->nnzb) * (A->br * A->br * vs + 4.0);
+}
+
+// The brick tables where the patterns suit (false: the two passes), and the A P scratch (with
+// bricks only where A P is wanted).  BLKAMG_PTAP_TUNE "nobrick" keeps the two passes.
+bool finish_plan(PtapPlan& pl, const bsr_s* A, const bsr_s* P, const bsr_s* C, bool want_ap, bool no_brick,
+                 hipStream_t s) {
+  const bool keep = want_ap && ap_cheaper(pl, A, P);
+  if (no_brick || !brick_symbolic(A, P, C, pl, keep, s)) pl.brick = BrickPlan{};
+  if (!pl.brick.on || pl.brick.keep_ap)
+    pl.ap_val.alloc(static_cast<size_t>(pl.ap_nslots) * P->br * P->bc * (A->dtype == BLKAMG_F64 ? 8 : 4));
+  return pl.brick.on;
+}
+
 template <int BR, int BC>
 void numeric_shape(const PtapPlan& pl, const bsr_s* A, const bsr_s* P, const bsr_s* R, bsr_s* C, hipStream_t s) {
   if (A->dtype == BLKAMG_F64)
@@ -717,6 +735,12 @@ extern "C" {
 int ptap_symbolic(bsr_t A, bsr_t P, bsr_t* C, void* stream) { return ptap_symbolic_ex(A, P, 0, C, stream); }
 
 int ptap_symbolic_ex(bsr_t A, bsr_t P, int flags, bsr_t* C, void* stream) {
+  return ptap_symbolic_for(A, P, flags, false, false, C, stream);
+}
+
+}  // extern "C"
+
+int blk::ptap_symbolic_for(bsr_s* A, bsr_s* P, int flags, bool once, bool want_ap, bsr_s** C, void* stream) {
   BLK_API_BEGIN
   BLK_REQUIRE((flags & ~(BLKAMG_PTAP_SYMMETRIC | BLKAMG_PTAP_HOST_SYMBOLIC)) == 0, BLKAMG_EINVAL,
               "unknown ptap flags");
@@ -735,7 +759,6 @@ int ptap_symbolic_ex(bsr_t A, bsr_t P, int flags, bsr_t* C, void* stream) {
   const char* tune = std::getenv("BLKAMG_PTAP_TUNE");
   const PtapTune tn{tune ? tune : "ap_sort"};
   const bool search = std::getenv("BLKAMG_PTAP_SEARCH") != nullptr;
-  const size_t acc_size = A->dtype == BLKAMG_F64 ? 8 : 4;
   ensure_host_pattern(P);
   bsr_s* R = transpose_of(P, s);
   if (!search && !(flags & BLKAMG_PTAP_HOST_SYMBOLIC) && !tn.has("host_symbolic")) {
@@ -749,16 +772,18 @@ int ptap_symbolic_ex(bsr_t A, bsr_t P, int flags, bsr_t* C, void* stream) {
     plan_settings(*plan, A, tn);
     DevBuf<int32_t> crp, cci;
     int64_t cnnz = 0;
-    if (ptap_symbolic_device(A, P, R, *plan, tn.has("ap_sort"), tn.has("c_sort"), crp, cci, cnnz, s)) {
+    if (ptap_symbolic_device(A, P, R, *plan, crp, cci, cnnz, s)) {
       BLK_REQUIRE(cnnz <= INT32_MAX, BLKAMG_EINVAL, "coarse pattern too large");
       plan->g_ap = pick_lanes(A->nbr ? static_cast<double>(plan->ap_nslots) / A->nbr : 0.0);
       plan->g_c = pick_lanes(P->nbc ? static_cast<double>(cnnz) / P->nbc : 0.0);
-      plan->ap_val.alloc(static_cast<size_t>(plan->ap_nslots) * P->br * P->bc * acc_size);
-      if (tn.has("nostage")) plan->ap_cap = plan->c_cap = 1;
       auto Cm = make_owned_device(P->nbc, P->nbc, P->bc, P->bc, A->dtype, std::move(crp), std::move(cci), cnnz, s);
-      Cm->ext = plan;
-      *C = Cm.release();
-      return BLKAMG_OK;
+      if (finish_plan(*plan, A, P, Cm.get(), want_ap, once || tn.has("nobrick"), s) ||
+          ptap_tables_device(A, P, R, *plan, tn.has("ap_sort"), tn.has("c_sort"), Cm->rowptr, cnnz, s)) {
+        if (tn.has("nostage")) plan->ap_cap = plan->c_cap = 1;
+        Cm->ext = plan;
+        *C = Cm.release();
+        return BLKAMG_OK;
+      }
     }
   }
   // host build
@@ -774,7 +799,7 @@ int ptap_symbolic_ex(bsr_t A, bsr_t P, int flags, bsr_t* C, void* stream) {
   plan->n_ap_rows = A->nbr;
   plan->g_ap = pick_lanes(A->nbr ? static_cast<double>(apci.size()) / A->nbr : 0.0);
   plan->g_c = pick_lanes(P->nbc ? static_cast<double>(cci.size()) / P->nbc : 0.0);
-  plan->ap_val.alloc(apci.size() * static_cast<size_t>(P->br) * P->bc * acc_size);
+  plan->ap_nslots = static_cast<int64_t>(apci.size());
   upload(plan->ap_rowptr, aprp);
   upload(plan->ap_colidx, apci);
   if (!search) {
@@ -810,7 +835,6 @@ int ptap_symbolic_ex(bsr_t A, bsr_t P, int flags, bsr_t* C, void* stream) {
     }
     build_pairs(R->nbr, P->nbc, R->h_rowptr, R->h_colidx, aprp, apci, orp, oci, true, plan->c_pairs);
     if (!plan->c_pairs.width) plan->sym = false;  // the searching kernel computes every block
-    plan->ap_nslots = static_cast<int64_t>(apci.size());
     plan_settings(*plan, A, tn);
     const int ap_spw = kBlock / plan->ap_nl, c_spw = kBlock / plan->c_nl;
     const std::vector<int32_t> ap_w = first_rows(aprp, ap_spw), c_w = first_rows(orp, c_spw);
@@ -848,11 +872,14 @@ int ptap_symbolic_ex(bsr_t A, bsr_t P, int flags, bsr_t* C, void* stream) {
     }
   }
   auto Cm = make_owned(P->nbc, P->nbc, P->bc, P->bc, A->dtype, std::move(crp), std::move(cci));
+  finish_plan(*plan, A, P, Cm.get(), want_ap, once || search || tn.has("nobrick"), s);
   Cm->ext = plan;
   HIP_CHECK(hipStreamSynchronize(s));
   *C = Cm.release();
   BLK_API_END
 }
+
+extern "C" {
 
 int ptap_numeric(bsr_t A, bsr_t P, bsr_t C, void* stream) {
   BLK_API_BEGIN
@@ -864,7 +891,9 @@ int ptap_numeric(bsr_t A, bsr_t P, bsr_t C, void* stream) {
               "pattern of A or P changed since ptap_symbolic");
   hipStream_t s = as_stream(stream);
   bsr_s* R = transpose_of(P, s);  // refreshes R values only if P's stamp moved
-  if (A->br == 3)
+  if (pl->brick.on)
+    brick_numeric(*pl, A, P, C, s);
+  else if (A->br == 3)
     numeric_shape<3, 6>(*pl, A, P, R, C, s);
   else
     numeric_shape<6, 6>(*pl, A, P, R, C, s);
@@ -885,7 +914,7 @@ int ptap_plan_info(bsr_t C, int64_t* ap_nnzb, int64_t* ap_pairs, int64_t* c_pair
   };
   if (ap_nnzb) *ap_nnzb = pl->ap_nslots;
   if (ap_pairs) *ap_pairs = total(pl->ap_pairs);
-  if (c_pairs) *c_pairs = total(pl->c_pairs);
+  if (c_pairs) *c_pairs = pl->brick.on ? pl->brick.n_codes : total(pl->c_pairs);
   if (symmetric) *symmetric = pl->sym ? 1 : 0;
   BLK_API_END
 }

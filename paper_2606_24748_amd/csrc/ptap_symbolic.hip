@@ -125,7 +125,7 @@ __device__ __forceinline__ void emit_row(int r, int n, const uint64_t* keys, con
       if (start) {
         const int u = ubase + __popcll(ball & ((1ull << lane) - 1ull));
         const int oidx = out_rp[r] + u;
-        out_ci[oidx] = static_cast<int32_t>(col);
+        if (out_ci) out_ci[oidx] = static_cast<int32_t>(col);
         if (pp) pp[oidx] = static_cast<int32_t>(cand_off[r] + p);
       }
       if (codes && valid) {
@@ -220,26 +220,31 @@ __global__ __launch_bounds__(64) void long_emit_kernel(int nlong, const int32_t*
   }
 }
 
-// Symmetric mode: for the u-th upper output (row a, column c) its index in the full
-// coarse pattern (the upper columns are the tail of the sorted full row) and its
-// mirror, the index of (c, a) (-1 on the diagonal).  A missing mirror or a mismatch
-// clears *ok.
+// Upper blocks (column >= row) of every coarse row: the tail of the sorted full row.
+__global__ void upper_count_kernel(int nrows, const int32_t* __restrict__ crp, const int32_t* __restrict__ cci,
+                                   int32_t* __restrict__ nu) {
+  const int a = blockIdx.x * blockDim.x + threadIdx.x;
+  if (a >= nrows) return;
+  int lo = crp[a], hi = crp[a + 1];
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (cci[mid] < a) lo = mid + 1; else hi = mid;
+  }
+  nu[a] = crp[a + 1] - lo;
+}
+
+// Per upper block (a, c): its index in the full coarse pattern and its mirror, the index
+// of (c, a) (-1 on the diagonal).  A missing mirror clears *ok.
 __global__ void sym_lists_kernel(int nrows, const int32_t* __restrict__ crp, const int32_t* __restrict__ cci,
-                                 const int32_t* __restrict__ orp, const int32_t* __restrict__ oci,
-                                 int32_t* __restrict__ uidx, int32_t* __restrict__ mirror, int* __restrict__ ok) {
+                                 const int32_t* __restrict__ orp, int32_t* __restrict__ uidx,
+                                 int32_t* __restrict__ mirror, int* __restrict__ ok) {
   const int a = blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= nrows) return;
   const int nu = orp[a + 1] - orp[a];
   const int first = crp[a + 1] - nu;
-  if (first < crp[a]) {  // more upper outputs than the full row holds
-    *ok = 0;
-    for (int u = 0; u < nu; ++u) uidx[orp[a] + u] = mirror[orp[a] + u] = crp[a];
-    return;
-  }
   for (int u = 0; u < nu; ++u) {
-    const int c = oci[orp[a] + u];
     const int t = first + u;
-    if (cci[t] != c) *ok = 0;
+    const int c = cci[t];
     uidx[orp[a] + u] = t;
     int m = -1;
     if (c != a) {
@@ -343,9 +348,10 @@ struct Product {
 // Out = X Y on device patterns (X: nrows rows, Y: ncols columns).  With `pairs`, also
 // the contribution list (codes, per-output starts, width, shift).  Rows with up to
 // kMaxCand contributions are sorted in LDS, longer ones in device memory.  False when
-// a row offset does not fit 16 bits or the codes would not fit 32 bits.
+// a row offset does not fit 16 bits or the codes would not fit 32 bits.  known: out.rp and
+// out.nout are there, only the pairs are built.
 bool product(int nrows, int ncols, const int32_t* x_rp, const int32_t* x_ci, const int32_t* y_rp,
-             const int32_t* y_ci, bool upper, PairList* pairs, Product& out, hipStream_t s) {
+             const int32_t* y_ci, bool upper, PairList* pairs, Product& out, hipStream_t s, bool known = false) {
   DevBuf<int64_t> ncand(static_cast<size_t>(std::max(nrows, 1)));
   DevBuf<int> maxima(3);
   HIP_CHECK(hipMemsetAsync(maxima.p, 0, 3 * sizeof(int), s));
@@ -404,9 +410,12 @@ bool product(int nrows, int ncols, const int32_t* x_rp, const int32_t* x_ci, con
     lkeys.release();
   }
   const int lgrid = std::max(1, std::min(nlong, 65536));
-  DevBuf<int32_t> nout(static_cast<size_t>(std::max(nrows, 1)));
-  out.rp.alloc(static_cast<size_t>(nrows) + 1);
-  if (nrows > 0) {
+  DevBuf<int32_t> nout;
+  if (!known) {
+    nout.alloc(static_cast<size_t>(std::max(nrows, 1)));
+    out.rp.alloc(static_cast<size_t>(nrows) + 1);
+  }
+  if (nrows > 0 && !known) {
     if (upper)
       prod_sort_kernel<true, true, 1><<<sgrid, 64, lds, s>>>(nrows, x_rp, x_ci, y_rp, y_ci, p2cap, ncand.p, nout.p,
                                                               nullptr, nullptr, nullptr, nullptr, nullptr, 0);
@@ -420,9 +429,11 @@ bool product(int nrows, int ncols, const int32_t* x_rp, const int32_t* x_ci, con
       HIP_CHECK(hipGetLastError());
     }
   }
-  const int32_t total_out = scan_total<int32_t>(nout.p, out.rp.p, nrows, s);
-  out.nout = total_out;
-  out.ci.alloc(static_cast<size_t>(total_out));
+  if (!known) {
+    out.nout = scan_total<int32_t>(nout.p, out.rp.p, nrows, s);
+    out.ci.alloc(static_cast<size_t>(out.nout));
+  }
+  const int32_t total_out = static_cast<int32_t>(out.nout);
   DevBuf<int64_t> coff;
   int width = 1, shift = 0;
   if (pairs) {
@@ -466,12 +477,11 @@ bool product(int nrows, int ncols, const int32_t* x_rp, const int32_t* x_ci, con
 
 // Workgroup tables of one pass: first rows, lane order, LDS capacity (99.5th
 // percentile of the X entries a workgroup spans, within kLdsBytes).
-void group_tables(const Product& o, const PairList& pl, int nrows, const int32_t* x_rp, int per, bool by_count,
+void group_tables(int64_t nout, const int32_t* rp, const PairList& pl, int nrows, const int32_t* x_rp, int per, bool by_count,
                   size_t per_entry_bytes, DevBuf<int32_t>& row0, DevBuf<uint8_t>& perm, int& cap, hipStream_t s) {
-  const int64_t nout = o.nout;
   const int ngroups = static_cast<int>((nout + per - 1) / per);
   row0.alloc(static_cast<size_t>(ngroups) + 1);
-  first_rows_kernel<<<(ngroups + 1 + 255) / 256, 256, 0, s>>>(ngroups, nrows, o.rp.p, per, row0.p);
+  first_rows_kernel<<<(ngroups + 1 + 255) / 256, 256, 0, s>>>(ngroups, nrows, rp, per, row0.p);
   HIP_CHECK(hipGetLastError());
   perm.alloc(std::max<size_t>(static_cast<size_t>(nout), 1));
   if (ngroups > 0) {
@@ -509,55 +519,70 @@ bool structural_product_device(int32_t nrows, int32_t ncols, const int32_t* x_rp
   return true;
 }
 
-bool ptap_symbolic_device(const bsr_s* A, const bsr_s* P, const bsr_s* R, PtapPlan& plan, bool ap_sort,
-                          bool c_sort, DevBuf<int32_t>& c_rowptr, DevBuf<int32_t>& c_colidx, int64_t& c_nnzb,
-                          hipStream_t s) {
+bool ptap_symbolic_device(const bsr_s* A, const bsr_s* P, const bsr_s* R, PtapPlan& plan, DevBuf<int32_t>& c_rowptr,
+                          DevBuf<int32_t>& c_colidx, int64_t& c_nnzb, hipStream_t s) {
   // A P (every product column an output)
   Product ap;
-  PairList ap_pairs;
+  PairList ap_pairs, c_pairs;
   if (!product(A->nbr, P->nbc, A->rowptr, A->colidx, P->rowptr, P->colidx, false, &ap_pairs, ap, s)) return false;
-  // the coarse pattern R (A P), and the outputs of the R AP pass
-  Product cfull, cup;
-  PairList c_pairs;
+  // the coarse pattern R (A P); its contributions too where every block is computed
+  Product cfull;
+  if (!product(R->nbr, P->nbc, R->rowptr, R->colidx, ap.rp.p, ap.ci.p, false, plan.sym ? nullptr : &c_pairs, cfull, s))
+    return false;
   if (plan.sym) {
-    if (!product(R->nbr, P->nbc, R->rowptr, R->colidx, ap.rp.p, ap.ci.p, false, nullptr, cfull, s)) return false;
-    if (!product(R->nbr, P->nbc, R->rowptr, R->colidx, ap.rp.p, ap.ci.p, true, &c_pairs, cup, s)) return false;
-    DevBuf<int32_t> uidx(static_cast<size_t>(std::max<int64_t>(cup.nout, 1)));
-    DevBuf<int32_t> mir(static_cast<size_t>(std::max<int64_t>(cup.nout, 1)));
+    const int grid = (R->nbr + 255) / 256;
+    DevBuf<int32_t> nu(static_cast<size_t>(std::max(R->nbr, 1))), up(static_cast<size_t>(R->nbr) + 1);
+    if (R->nbr > 0) {
+      upper_count_kernel<<<grid, 256, 0, s>>>(R->nbr, cfull.rp.p, cfull.ci.p, nu.p);
+      HIP_CHECK(hipGetLastError());
+    }
+    plan.c_nslots = scan_total<int32_t>(nu.p, up.p, R->nbr, s);
+    DevBuf<int32_t> uidx(static_cast<size_t>(std::max<int64_t>(plan.c_nslots, 1)));
+    DevBuf<int32_t> mir(static_cast<size_t>(std::max<int64_t>(plan.c_nslots, 1)));
     DevBuf<int> ok(1);
     const int one = 1;
     HIP_CHECK(hipMemcpyAsync(ok.p, &one, sizeof(int), hipMemcpyHostToDevice, s));
     if (R->nbr > 0) {
-      sym_lists_kernel<<<(R->nbr + 255) / 256, 256, 0, s>>>(R->nbr, cfull.rp.p, cfull.ci.p, cup.rp.p, cup.ci.p,
-                                                             uidx.p, mir.p, ok.p);
+      sym_lists_kernel<<<grid, 256, 0, s>>>(R->nbr, cfull.rp.p, cfull.ci.p, up.p, uidx.p, mir.p, ok.p);
       HIP_CHECK(hipGetLastError());
     }
     int h = 0;
     HIP_CHECK(hipMemcpyAsync(&h, ok.p, sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));
     BLK_REQUIRE(h == 1, BLKAMG_EINVAL, "coarse pattern is not symmetric");
-    plan.c_nslots = cup.nout;
+    plan.c_up_rp = std::move(up);
     plan.c_up_idx = std::move(uidx);
     plan.c_mirror = std::move(mir);
-  } else {
-    if (!product(R->nbr, P->nbc, R->rowptr, R->colidx, ap.rp.p, ap.ci.p, false, &c_pairs, cfull, s)) return false;
   }
-  const Product& cout_ = plan.sym ? cup : cfull;
-  const int ap_spw = kBlock / plan.ap_nl, c_spw = kBlock / plan.c_nl;
-  group_tables(ap, ap_pairs, A->nbr, A->rowptr, ap_spw, ap_sort,
-               4 + static_cast<size_t>(A->br) * A->br * dtype_size(A->dtype), plan.ap_slot_row0, plan.ap_perm,
-               plan.ap_cap, s);
-  group_tables(cout_, c_pairs, R->nbr, R->rowptr, c_spw, c_sort, 4, plan.c_slot_row0, plan.c_perm, plan.c_cap, s);
-  HIP_CHECK(hipStreamSynchronize(s));
   plan.ap_nslots = ap.nout;
   plan.ap_pairs = std::move(ap_pairs);
   plan.c_pairs = std::move(c_pairs);
-  if (plan.sym) plan.c_up_rp = std::move(cup.rp);
   plan.ap_rowptr = std::move(ap.rp);
   plan.ap_colidx = std::move(ap.ci);
   c_nnzb = cfull.nout;
   c_rowptr = std::move(cfull.rp);
   c_colidx = std::move(cfull.ci);
+  return true;
+}
+
+bool ptap_tables_device(const bsr_s* A, const bsr_s* P, const bsr_s* R, PtapPlan& plan, bool ap_sort, bool c_sort,
+                        const int32_t* c_rowptr, int64_t c_nnzb, hipStream_t s) {
+  if (plan.sym) {
+    Product cup;
+    cup.nout = plan.c_nslots;
+    cup.rp = std::move(plan.c_up_rp);
+    const bool ok = product(R->nbr, P->nbc, R->rowptr, R->colidx, plan.ap_rowptr.p, plan.ap_colidx.p, true,
+                            &plan.c_pairs, cup, s, true);
+    plan.c_up_rp = std::move(cup.rp);
+    if (!ok) return false;
+  }
+  const int ap_spw = kBlock / plan.ap_nl, c_spw = kBlock / plan.c_nl;
+  group_tables(plan.ap_nslots, plan.ap_rowptr.p, plan.ap_pairs, A->nbr, A->rowptr, ap_spw, ap_sort,
+               4 + static_cast<size_t>(A->br) * A->br * dtype_size(A->dtype), plan.ap_slot_row0, plan.ap_perm,
+               plan.ap_cap, s);
+  group_tables(plan.sym ? plan.c_nslots : c_nnzb, plan.sym ? plan.c_up_rp.p : c_rowptr, plan.c_pairs, R->nbr,
+               R->rowptr, c_spw, c_sort, 4, plan.c_slot_row0, plan.c_perm, plan.c_cap, s);
+  HIP_CHECK(hipStreamSynchronize(s));
   return true;
 }
 
