@@ -92,7 +92,8 @@ struct amg_s {
   blk::DevBuf<double> pcg_s;           // single-system CG scalars
   blk::DevBuf<int> flags;              // [0] non-SPD pivot, [1] singular diagonal block
   blk::DevBuf<double> pr, pz, pp, pw;  // CG vectors (F64, [n_dof][nrhs])
-  double* host_s = nullptr;            // pinned mirror of the single-system CG scalars
+  double* host_s = nullptr;            // the single-system CG scalars as the device writes them to the host
+  hipEvent_t pcg_ev = nullptr;         // ... have been written
   // batched CG
   blk::SegGrid fgrid[2];               // fine-level dot grids for 1 and 8 right-hand sides
   blk::DevBuf<int32_t> d_fine_dof_off;
@@ -136,6 +137,7 @@ struct amg_s {
     if (gs) (void)hipStreamDestroy(gs);
     for (auto& e : ev)
       if (e) (void)hipEventDestroy(e);
+    if (pcg_ev) (void)hipEventDestroy(pcg_ev);
     if (host_s) (void)hipHostFree(host_s);
     if (host_stat) (void)hipHostFree(host_stat);
   }
@@ -147,8 +149,6 @@ namespace {
 // ---------------------------------------------------------------------------
 // Single-system reductions (fused CG path)
 // ---------------------------------------------------------------------------
-enum RedOp { R_STORE = 0, R_SQRT, R_ALPHA, R_BETA };
-
 __global__ __launch_bounds__(256) void reduce_chunks_kernel(const double* __restrict__ partial, int n, int chunk,
                                                             double* __restrict__ out) {
   __shared__ double lds[4];
@@ -159,32 +159,9 @@ __global__ __launch_bounds__(256) void reduce_chunks_kernel(const double* __rest
   if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-__global__ __launch_bounds__(256) void reduce_kernel(const double* __restrict__ partial, int n, double* dst, int op,
-                                                     double* pcg) {
-  __shared__ double lds[4];
-  double v = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) v += partial[i];
-  const double s = block_sum_256(v, lds);
-  if (threadIdx.x == 0) {
-    switch (op) {
-      case R_STORE: *dst = s; break;
-      case R_SQRT: *dst = sqrt(s > 0.0 ? s : 0.0); break;
-      case R_ALPHA:  // s = p.w
-        pcg[S_PW] = s;
-        if (!(s > 0.0)) { pcg[S_FLAG] = 1.0; pcg[S_ALPHA] = 0.0; }
-        else pcg[S_ALPHA] = pcg[S_RZ] / s;
-        break;
-      case R_BETA:  // s = r.z (new)
-        pcg[S_BETA] = s / pcg[S_RZ];
-        pcg[S_RZ] = s;
-        break;
-    }
-  }
-}
-
-// Many partials are first summed to 256 (fixed chunks); n becomes the number left.
-const double* reduce_chunks(amg_s* M, int& n, hipStream_t s) {
-  if (n <= 4096) return M->partial.p;
+// More than `most` partials are first summed to 256 (fixed chunks); n becomes the number left.
+const double* reduce_chunks(amg_s* M, int& n, hipStream_t s, int most = 4096) {
+  if (n <= most) return M->partial.p;
   const int chunks = 256;
   reduce_chunks_kernel<<<chunks, 256, 0, s>>>(M->partial.p, n, (n + chunks - 1) / chunks, M->partial2.p);
   HIP_CHECK(hipGetLastError());
@@ -209,14 +186,9 @@ void sum_finish(amg_s* M, int n, const Op& op, hipStream_t s) {
   HIP_CHECK(hipGetLastError());
 }
 
-void reduce(amg_s* M, int n, double* dst, int op, hipStream_t s) {
-  const double* src = reduce_chunks(M, n, s);
-  reduce_kernel<<<1, 256, 0, s>>>(src, n, dst, op, M->pcg_s.p);
-  HIP_CHECK(hipGetLastError());
-}
-
 inline int vgrid(size_t n) { return static_cast<int>((n + 255) / 256); }
-inline int rgrid(size_t n) { return static_cast<int>(std::max<size_t>(1, std::min<size_t>((n + 255) / 256, 2048))); }
+constexpr int kDotGrid = 2048;  // workgroups of a dot product at most
+inline int rgrid(size_t n) { return static_cast<int>(std::max<size_t>(1, std::min<size_t>((n + 255) / 256, kDotGrid))); }
 
 template <class TV>
 TV* buf(DevBuf<char>& b) { return reinterpret_cast<TV*>(b.p); }
@@ -1192,10 +1164,11 @@ std::unique_ptr<amg_s> new_amg(const blkamg_opts& o, bsr_s* A0, int32_t n_inst, 
   const size_t nsc = static_cast<size_t>(o.max_levels) * n_inst;
   M->sc.alloc(nsc);
   zero_now(M->sc.p, nsc * sizeof(LevelScalars));
-  M->partial.alloc(static_cast<size_t>(A0->nbr) / 4 + 8192);
+  M->partial.alloc(static_cast<size_t>(A0->nbr) / 4 + 8192 + 2 * kDotGrid);
   M->partial2.alloc(256);
   M->pcg_s.alloc(S_COUNT);
-  HIP_CHECK(hipHostMalloc(reinterpret_cast<void**>(&M->host_s), S_COUNT * sizeof(double)));
+  HIP_CHECK(hipHostMalloc(reinterpret_cast<void**>(&M->host_s), S_COUNT * sizeof(double), hipHostMallocCoherent));
+  HIP_CHECK(hipEventCreateWithFlags(&M->pcg_ev, hipEventDisableTiming));
   HIP_CHECK(hipHostMalloc(reinterpret_cast<void**>(&M->host_stat), 4 * sizeof(int32_t)));
   M->bstat.alloc(4);
   return M;
@@ -1454,8 +1427,10 @@ Level* get_level(amg_s* M, int32_t l) {
 // ---------------------------------------------------------------------------
 // CG
 // ---------------------------------------------------------------------------
-// One system, one right-hand side: the SpMV with the p.w dot fused in, one 8-byte
-// read per iteration for the stopping test.
+// One system, one right-hand side: the SpMV with the p.w dot fused in, the scalars formed by
+// the kernels that use them, and written to the host once per iteration for the stopping test.
+// A step on 9^3 elements (21 iterations, bound by launches): 1.77 -> 1.30 ms against one launch
+// per scalar, a copy, and a wait before the V-cycle; 45^3, FP32 hierarchy: 5.83 -> 5.61 ms.
 int pcg_single(bsr_s* A, amg_s* M, const double* d_b, double* d_x, double rtol, int32_t maxit, int32_t* iters,
                double* relres, hipStream_t s) {
   const size_t n = static_cast<size_t>(M->lv[0]->n);
@@ -1474,11 +1449,18 @@ int pcg_single(bsr_s* A, amg_s* M, const double* d_b, double* d_x, double rtol, 
   double* sc = M->pcg_s.p;
   const int vg = rgrid(n);
   HIP_CHECK(hipMemsetAsync(sc, 0, S_COUNT * sizeof(double), s));
-  pcg_init_kernel<<<vg, 256, 0, s>>>(n, d_b, d_x, r, M->partial.p);
+  // partial sums of r.r and r.z, apart from the product's of p.w
+  double* rr_part = M->partial.p + (M->partial.n - 2 * kDotGrid);
+  double* rz_part = rr_part + kDotGrid;
+  auto to_host = [&](int field, int rz) {
+    pcg_store_kernel<<<1, 256, 0, s>>>(rr_part, vg, sc, field, rz, M->host_s);
+    HIP_CHECK(hipGetLastError());
+    HIP_CHECK(hipEventRecord(M->pcg_ev, s));
+  };
+  pcg_init_kernel<<<vg, 256, 0, s>>>(n, d_b, d_x, r, rr_part);
   HIP_CHECK(hipGetLastError());
-  reduce(M, vg, sc + S_BB, R_STORE, s);
-  HIP_CHECK(hipMemcpyAsync(M->host_s, sc, S_COUNT * sizeof(double), hipMemcpyDeviceToHost, s));
-  HIP_CHECK(hipStreamSynchronize(s));
+  to_host(S_BB, S_RZ);
+  HIP_CHECK(hipEventSynchronize(M->pcg_ev));
   const double bn = std::sqrt(M->host_s[S_BB]);
   int32_t it = 0;
   double rn = bn;
@@ -1492,16 +1474,17 @@ int pcg_single(bsr_s* A, amg_s* M, const double* d_b, double* d_x, double rtol, 
   auto precondition = [&]() {
     if (mixed) {
       const float* z32 = vcycle_f32_in_place(M, s);
-      dot_kernel<float><<<vg, 256, 0, s>>>(n, r, z32, M->partial.p);
+      dot_kernel<float><<<vg, 256, 0, s>>>(n, r, z32, rz_part);
       return z32;
     }
     vcycle(M, r, z, 1, s);
-    dot_kernel<double><<<vg, 256, 0, s>>>(n, r, z, M->partial.p);
+    dot_kernel<double><<<vg, 256, 0, s>>>(n, r, z, rz_part);
     return static_cast<const float*>(nullptr);
   };
-  auto direction = [&](const float* z32, int use_beta) {
-    if (mixed) pcg_p_kernel<float><<<vgrid(n), 256, 0, s>>>(n, sc, use_beta, z32, p);
-    else pcg_p_kernel<double><<<vgrid(n), 256, 0, s>>>(n, sc, use_beta, z, p);
+  int rz = S_RZ;  // where r.z of the current direction lies
+  auto direction = [&](const float* z32, int old) {
+    if (mixed) pcg_p_kernel<float><<<vg, 256, 0, s>>>(n, rz_part, vg, sc, old, rz, z32, p);
+    else pcg_p_kernel<double><<<vg, 256, 0, s>>>(n, rz_part, vg, sc, old, rz, z, p);
     HIP_CHECK(hipGetLastError());
   };
   if (mixed) {
@@ -1511,8 +1494,7 @@ int pcg_single(bsr_s* A, amg_s* M, const double* d_b, double* d_x, double rtol, 
   {
     const float* z32 = precondition();
     HIP_CHECK(hipGetLastError());
-    reduce(M, vg, sc + S_RZ, R_STORE, s);
-    direction(z32, 0);
+    direction(z32, -1);
   }
   const int32_t* mir = M->o.sym_spmv ? symmetric_mirror(A, s) : nullptr;
   const int G = lanes_for_reads(A, 1, mir);
@@ -1522,26 +1504,36 @@ int pcg_single(bsr_s* A, amg_s* M, const double* d_b, double* d_x, double rtol, 
   // interval misses the top of the spectrum makes the V-cycle indefinite)
   const bool guard = M->guard_armed;
   constexpr double kGuardGrowth = 1e3;
-  double rmin = bn;
+  double rmin = bn, rn_before = bn;
   while (it < maxit) {
     EpiPcgW epi{p, w, M->partial.p};
-    const int sg = A->br == 3 ? launch_rows<3, 3, 1, double, double, double>(G, A->nbr, A->rowptr, A->colidx,
+    int sg = A->br == 3 ? launch_rows<3, 3, 1, double, double, double>(G, A->nbr, A->rowptr, A->colidx,
                                                                             static_cast<const double*>(A->val), p, epi, s,
                                                                             mir, A->sym_dist)
                               : launch_rows<6, 6, 1, double, double, double>(G, A->nbr, A->rowptr, A->colidx,
                                                                             static_cast<const double*>(A->val), p, epi, s,
                                                                             mir, A->sym_dist);
-    reduce(M, sg, nullptr, R_ALPHA, s);
-    pcg_update_kernel<<<vg, 256, 0, s>>>(n, sc, p, w, d_x, r, M->partial.p, r32);
+    const double* pw = reduce_chunks(M, sg, s, kDotGrid);
+    pcg_update_kernel<<<vg, 256, 0, s>>>(n, pw, sg, sc, rz, p, w, d_x, r, rr_part, r32);
     HIP_CHECK(hipGetLastError());
-    reduce(M, vg, sc + S_RR, R_STORE, s);
+    to_host(S_RR, rz);
     ++it;
-    HIP_CHECK(hipMemcpyAsync(M->host_s, sc, S_COUNT * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_CHECK(hipStreamSynchronize(s));
+    // The next V-cycle is queued before the host waits for the residual, unless the last
+    // reduction suggests that this one may be the last: otherwise the device idles 20 - 25 us
+    // while the host wakes and launches (of 75 us an iteration for 1000 rows).
+    const bool ahead = it < maxit && rn * (rn / rn_before) > 3.0 * rtol * bn;
+    const float* z32 = nullptr;
+    if (ahead) {
+      z32 = precondition();
+      HIP_CHECK(hipGetLastError());
+    }
+    HIP_CHECK(hipEventSynchronize(M->pcg_ev));
     if (M->host_s[S_FLAG] != 0.0) {
       if (iters) *iters = it;
+      HIP_CHECK(hipStreamSynchronize(s));
       fail(BLKAMG_EBREAKDOWN, "CG breakdown: p^T A p <= 0");
     }
+    rn_before = rn;
     rn = std::sqrt(M->host_s[S_RR]);
     if (guard && (!(M->host_s[S_RZ] > 0.0) || !std::isfinite(rn) || rn > kGuardGrowth * rmin)) {
       mlp_fallback_all(M, s);
@@ -1549,11 +1541,19 @@ int pcg_single(bsr_s* A, amg_s* M, const double* d_b, double* d_x, double rtol, 
       return pcg_single(A, M, d_b, d_x, rtol, maxit, iters, relres, s);
     }
     rmin = std::min(rmin, rn);
-    if (rn <= rtol * bn) { converged = true; break; }
-    const float* z32 = precondition();
-    HIP_CHECK(hipGetLastError());
-    reduce(M, vg, nullptr, R_BETA, s);
-    direction(z32, 1);
+    if (rn <= rtol * bn) {
+      converged = true;
+      if (ahead) HIP_CHECK(hipStreamSynchronize(s));  // nothing of the hierarchy is in use at return
+      break;
+    }
+    if (it >= maxit) break;
+    if (!ahead) {
+      z32 = precondition();
+      HIP_CHECK(hipGetLastError());
+    }
+    const int old = rz;
+    rz = rz == S_RZ ? S_RZ1 : S_RZ;
+    direction(z32, old);
   }
   if (iters) *iters = it;
   if (relres) *relres = rn / bn;

@@ -859,7 +859,34 @@ __global__ void cast_vec_kernel(size_t n, const TI* __restrict__ a, TO* __restri
 // ---------------------------------------------------------------------------
 // Single-system CG kernels (fused path)
 // ---------------------------------------------------------------------------
-enum { S_RZ = 0, S_PW, S_ALPHA, S_RR, S_BETA, S_BB, S_FLAG, S_COUNT };
+// S_RZ / S_RZ1 take turns: r.z of this iteration and of the one before
+enum { S_RZ = 0, S_RZ1, S_RR, S_BB, S_FLAG, S_COUNT };
+
+// The sum of n partials (fixed order) in every thread of a 256-thread workgroup.
+__device__ __forceinline__ double sum_partials(const double* __restrict__ partial, int n) {
+  __shared__ double lds[4];
+  __shared__ double all;
+  double v = 0.0;
+  for (int i = threadIdx.x; i < n; i += 256) v += partial[i];
+  const double s = block_sum_256(v, lds);
+  if (threadIdx.x == 0) all = s;
+  __syncthreads();
+  return all;
+}
+
+// sc[field] = sum of n partials; the host's copies of it, of r.z and of the flag
+__global__ __launch_bounds__(256) void pcg_store_kernel(const double* __restrict__ partial, int n,
+                                                        double* __restrict__ sc, int field, int rz,
+                                                        double* __restrict__ host) {
+  const double s = sum_partials(partial, n);
+  if (threadIdx.x == 0) {
+    sc[field] = s;
+    host[field] = s;
+    host[S_RZ] = sc[rz];
+    host[S_FLAG] = sc[S_FLAG];
+    __threadfence_system();
+  }
+}
 
 struct EpiPcgW {
   static constexpr bool kReduce = true;
@@ -886,14 +913,19 @@ struct EpiPcgW {
 };
 
 // x += alpha p, r -= alpha w, partial sums of r.r; with r32 set, also the FP32 copy of r
-// that an FP32 V-cycle takes as input (rounded to nearest)
-__global__ __launch_bounds__(256) void pcg_update_kernel(size_t n, const double* __restrict__ sc,
+// that an FP32 V-cycle takes as input (rounded to nearest).  Every workgroup adds the np
+// partial sums of p.w itself and forms alpha = r.z / p.w (0, and the flag set, unless
+// p.w > 0): a launch for that sum alone took 4 - 5 us.
+__global__ __launch_bounds__(256) void pcg_update_kernel(size_t n, const double* __restrict__ pw, int np,
+                                                         double* __restrict__ sc, int rz,
                                                          const double* __restrict__ p, const double* __restrict__ w,
                                                          double* __restrict__ x, double* __restrict__ r,
                                                          double* __restrict__ partial, float* __restrict__ r32) {
   __shared__ double lds[4];
   double acc = 0.0;
-  const double a = sc[S_ALPHA];
+  const double d = sum_partials(pw, np);
+  const double a = d > 0.0 ? sc[rz] / d : 0.0;
+  if (!(d > 0.0) && blockIdx.x == 0 && threadIdx.x == 0) sc[S_FLAG] = 1.0;
   for (size_t g = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; g < n;
        g += static_cast<size_t>(gridDim.x) * blockDim.x) {
     x[g] = fmadd(a, p[g], x[g]);
@@ -919,13 +951,20 @@ __global__ __launch_bounds__(256) void dot_kernel(size_t n, const double* __rest
   if (threadIdx.x == 0) partial[blockIdx.x] = t;
 }
 
+// p = z + beta p, beta = r.z / the previous r.z (old < 0: p = z).  Every workgroup adds the
+// np partial sums of r.z itself; the first keeps it as sc[now].
 template <class TZ>
-__global__ void pcg_p_kernel(size_t n, const double* __restrict__ sc, int use_beta, const TZ* __restrict__ z,
-                             double* __restrict__ p) {
-  const size_t g = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
-  if (g >= n) return;
-  const double zv = static_cast<double>(z[g]);
-  p[g] = use_beta ? fmadd(sc[S_BETA], p[g], zv) : zv;
+__global__ __launch_bounds__(256) void pcg_p_kernel(size_t n, const double* __restrict__ rz, int np,
+                                                    double* __restrict__ sc, int old, int now,
+                                                    const TZ* __restrict__ z, double* __restrict__ p) {
+  const double s = sum_partials(rz, np);
+  const double beta = old >= 0 ? s / sc[old] : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) sc[now] = s;
+  for (size_t g = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; g < n;
+       g += static_cast<size_t>(gridDim.x) * blockDim.x) {
+    const double zv = static_cast<double>(z[g]);
+    p[g] = old >= 0 ? fmadd(beta, p[g], zv) : zv;
+  }
 }
 
 __global__ __launch_bounds__(256) void pcg_init_kernel(size_t n, const double* __restrict__ b, double* __restrict__ x,
