@@ -124,53 +124,63 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Stream mode.  After the Jacobians, lane 8n + q forms the physical gradient of shape
-// function n at Gauss point q once, so the per-block loop over the points only forms
-// outer products (about a third of the FP64 work of forming both gradients in every
-// lane).  One LDS buffer per wave holds the geometry and the gradients, then the 64
-// output blocks, which leave as one contiguous 4.6 KB run of 16-byte non-temporal
-// stores: the stream is read back only by the assembly, long after.
-// 128^3 distorted elements: 2.2 ms against 3.4 ms for the block-per-lane gradients
-// with workgroup barriers and plain stores.
+// Stream mode.  A wave takes E consecutive elements: lane 8i + q forms the Jacobian of element
+// i at Gauss point q.  Then, element by element, lane 8n + q forms the physical gradient of
+// shape function n at point q once, so the per-block loop over the points only forms outer
+// products (about a third of the FP64 work of forming both gradients in every lane).  One LDS
+// buffer per wave holds the gradients, then the 64 output blocks, which leave as one
+// contiguous 4.6 KB run of 16-byte non-temporal stores: the stream is read back only by the
+// assembly, long after.  128^3 distorted elements: 2.2 ms with E = 1, against 3.4 ms for the
+// block-per-lane gradients with workgroup barriers and plain stores.
+// With E = 1 the Jacobians, 170 of 370 vector instructions, ran on 8 of 64 lanes, and every
+// element waited for its nodes and coordinates in turn; E = 8 fills the lanes (220 instructions
+// an element) and waits once for eight: 97^3 elements 0.95 -> 0.83 ms (5.1 TB/s written, where
+// a copy reads and writes 5.7 together), 60^3 0.22 -> 0.20 ms.
+template <int E>
 __global__ __launch_bounds__(256) void fe_stream_kernel(int64_t count, const int32_t* __restrict__ elem_nodes,
                                                         const double* __restrict__ coords,
                                                         const double* __restrict__ lam,
                                                         const double* __restrict__ mu, double* __restrict__ out) {
-  constexpr int kGradOff = 8 * kFeGeo;  // geometry [8][kFeGeo], then gradients [q][n][3]
-  static_assert(kGradOff + 8 * 8 * 3 <= 64 * 9, "geometry and gradients fit in the block buffer");
-  __shared__ __align__(16) double buf[kFeWaves][64 * 9];
+  __shared__ __align__(16) double buf[kFeWaves][64 * 9];  // gradients [q][n][3], then blocks
+  __shared__ double geos[kFeWaves][E][8 * kFeGeo];
   const int w = static_cast<int>(threadIdx.x) / 64, lane = static_cast<int>(threadIdx.x) % 64;
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * kFeWaves + w;
-  if (e >= count) return;
-  double* geo = buf[w];
-  double* grad = buf[w] + kGradOff;
-  if (lane < 8) {
+  const int64_t e0 = (static_cast<int64_t>(blockIdx.x) * kFeWaves + w) * E;
+  if (e0 >= count) return;
+  const int ne = static_cast<int>(min(static_cast<int64_t>(E), count - e0));
+  double* grad = buf[w];
+  double l_lane = 0.0, m_lane = 0.0;  // lane i: element i
+  if (lane < ne) {
+    l_lane = lam[e0 + lane];
+    m_lane = mu[e0 + lane];
+  }
+  if (lane < 8 * ne) {
     const double x = gauss_coord(lane & 1), y = gauss_coord((lane >> 1) & 1), z = gauss_coord((lane >> 2) & 1);
-    jacobian_point(elem_nodes + e * 8, coords, x, y, z, geo + lane * kFeGeo);
+    jacobian_point(elem_nodes + (e0 + (lane >> 3)) * 8, coords, x, y, z, geos[w][lane >> 3] + (lane & 7) * kFeGeo);
   }
-  wave_sync();
-  {
-    const int n = lane >> 3, q = lane & 7;
-    double rg[3];
-    ref_grad(n, gauss_coord(q & 1), gauss_coord((q >> 1) & 1), gauss_coord((q >> 2) & 1), rg);
-    phys_grad(rg, geo + q * kFeGeo, grad + (q * 8 + n) * 3);
+  const int n = lane >> 3, q0 = lane & 7;  // also the output block (n, q0)
+  double rg[3];
+  ref_grad(n, gauss_coord(q0 & 1), gauss_coord((q0 >> 1) & 1), gauss_coord((q0 >> 2) & 1), rg);
+#pragma unroll 1
+  for (int i = 0; i < ne; ++i) {
+    const double* geo = geos[w][i];
+    wave_sync();  // geometry written; the last element's blocks have been read
+    phys_grad(rg, geo + q0 * kFeGeo, grad + (q0 * 8 + n) * 3);
+    wave_sync();
+    double S[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      add_point(geo[q * kFeGeo + 9], grad + (q * 8 + n) * 3, grad + (q * 8 + q0) * 3, S);
+    double K[9];
+    element_block(__shfl(l_lane, i), __shfl(m_lane, i), S, K);
+    wave_sync();  // every lane has read the gradients before the blocks overwrite them
+#pragma unroll
+    for (int t = 0; t < 9; ++t) buf[w][lane * 9 + t] = K[t];
+    wave_sync();
+    using v2 = double __attribute__((ext_vector_type(2)));
+    const v2* src = reinterpret_cast<const v2*>(buf[w]);
+    v2* dst = reinterpret_cast<v2*>(out + (e0 + i) * 64 * 9);
+    for (int k = lane; k < 64 * 9 / 2; k += 64) __builtin_nontemporal_store(src[k], dst + k);
   }
-  wave_sync();
-  const int a = lane >> 3, b = lane & 7;
-  double S[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-  for (int q = 0; q < 8; ++q)
-    add_point(geo[q * kFeGeo + 9], grad + (q * 8 + a) * 3, grad + (q * 8 + b) * 3, S);
-  double K[9];
-  element_block(lam[e], mu[e], S, K);
-  wave_sync();  // every lane has read the gradients before the blocks overwrite them
-#pragma unroll
-  for (int t = 0; t < 9; ++t) buf[w][lane * 9 + t] = K[t];
-  wave_sync();
-  using v2 = double __attribute__((ext_vector_type(2)));
-  const v2* src = reinterpret_cast<const v2*>(buf[w]);
-  v2* dst = reinterpret_cast<v2*>(out + e * 64 * 9);
-  for (int k = lane; k < 64 * 9 / 2; k += 64) __builtin_nontemporal_store(src[k], dst + k);
 }
 
 // Element-by-element modes: the same arithmetic, with each lane forming the gradients
@@ -249,10 +259,17 @@ void launch_fe(int64_t count, const int32_t* order, const int32_t* elem_nodes, c
   if (count <= 0) return;
   const int64_t grid = grid_of(count);
   BLK_REQUIRE(grid <= INT32_MAX, BLKAMG_EINVAL, "too many elements for one launch");
-  if constexpr (kMode == kStream)
-    fe_stream_kernel<<<static_cast<int>(grid), 256, 0, s>>>(count, elem_nodes, coords, lam, mu, out);
-  else
+  if constexpr (kMode == kStream) {
+    // below 48 k elements the shorter waves are as fast or faster (27 k: 33 against 35 - 37 us,
+    // with too few long waves to fill the chip; 64 k: 61 - 67 against 61 - 64 us)
+    if (count >= 48 * 1024) {
+      fe_stream_kernel<8><<<static_cast<int>((grid + 7) / 8), 256, 0, s>>>(count, elem_nodes, coords, lam, mu, out);
+    } else {
+      fe_stream_kernel<1><<<static_cast<int>(grid), 256, 0, s>>>(count, elem_nodes, coords, lam, mu, out);
+    }
+  } else {
     fe_q1_kernel<kMode><<<static_cast<int>(grid), 256, 0, s>>>(count, order, elem_nodes, coords, lam, mu, slot, out);
+  }
   HIP_CHECK(hipGetLastError());
 }
 
