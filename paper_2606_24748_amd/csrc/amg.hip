@@ -1564,7 +1564,6 @@ int pcg_single(bsr_s* A, amg_s* M, const double* d_b, double* d_x, double rtol, 
 // test kept on the device; a stopped system is frozen (alpha = 0).
 template <int NR>
 void bpcg_iteration(amg_s* M, bsr_s* A, double* x, double rtol, int maxit, hipStream_t s) {
-  const size_t nrow = static_cast<size_t>(M->lv[0]->n);
   const int nseg = M->n_inst;
   const int stride = nseg * NR;
   double* bs = M->bsc.p;
@@ -1574,24 +1573,23 @@ void bpcg_iteration(amg_s* M, bsr_s* A, double* x, double rtol, int maxit, hipSt
   double* z = M->pz.p;
   double* p = M->pp.p;
   double* w = M->pw.p;
-  const int vg = vgrid(nrow * NR);
   spmv(A, 1.0, p, 0.0, w, BLKAMG_F64, NR, s);
   seg_reduce<NR>(M, g, p, w, OpBAlpha{bs, stride, NR}, s);
   // with an FP32 hierarchy the update writes the V-cycle's FP32 input and the reads of
   // its output widen FP32 values (no separate casts)
   const bool mixed = M->T == BLKAMG_F32;
   float* r32 = mixed ? buf<float>(M->lv[0]->f) : nullptr;
-  bpcg_axpy_kernel<<<vg, 256, 0, s>>>(nrow, NR, off, nseg, bs, stride, p, w, x, r, r32);
+  bpcg_axpy_kernel<NR><<<g.nchunk, 256, 0, s>>>(g.lo.p, g.hi.p, off, nseg, bs, stride, p, w, x, r, r32, M->partial.p);
   HIP_CHECK(hipGetLastError());
-  seg_reduce<NR>(M, g, r, r, OpBRr{bs, stride, NR, maxit, rtol}, s);
+  seg_finish(M, g, NR, OpBRr{bs, stride, NR, maxit, rtol}, s);
   if (mixed) {
     const float* z32 = vcycle_f32_in_place<NR>(M, s);
     seg_reduce<NR>(M, g, r, z32, OpBBeta{bs, stride, NR}, s);
-    bpcg_p_kernel<float><<<vg, 256, 0, s>>>(nrow, NR, off, nseg, bs, stride, 1, z32, p);
+    bpcg_p_kernel<NR, float><<<g.nchunk, 256, 0, s>>>(g.lo.p, g.hi.p, off, nseg, bs, stride, 1, z32, p);
   } else {
     vcycle(M, r, z, NR, s);
     seg_reduce<NR>(M, g, r, z, OpBBeta{bs, stride, NR}, s);
-    bpcg_p_kernel<double><<<vg, 256, 0, s>>>(nrow, NR, off, nseg, bs, stride, 1, z, p);
+    bpcg_p_kernel<NR, double><<<g.nchunk, 256, 0, s>>>(g.lo.p, g.hi.p, off, nseg, bs, stride, 1, z, p);
   }
   HIP_CHECK(hipGetLastError());
 }
@@ -1671,11 +1669,11 @@ int pcg_batched(bsr_s* A, amg_s* M, const double* d_b, double* d_x, double rtol,
     HIP_CHECK(hipGetLastError());
     const float* z32 = vcycle_f32_in_place<NR>(M, s);
     seg_reduce<NR>(M, g, M->pr.p, z32, OpBRz0{bs, stride, NR}, s);
-    bpcg_p_kernel<float><<<vgrid(n), 256, 0, s>>>(nrow, NR, off, M->n_inst, bs, stride, 0, z32, M->pp.p);
+    bpcg_p_kernel<NR, float><<<g.nchunk, 256, 0, s>>>(g.lo.p, g.hi.p, off, M->n_inst, bs, stride, 0, z32, M->pp.p);
   } else {
     vcycle(M, M->pr.p, M->pz.p, NR, s);
     seg_reduce<NR>(M, g, M->pr.p, M->pz.p, OpBRz0{bs, stride, NR}, s);
-    bpcg_p_kernel<double><<<vgrid(n), 256, 0, s>>>(nrow, NR, off, M->n_inst, bs, stride, 0, M->pz.p, M->pp.p);
+    bpcg_p_kernel<NR, double><<<g.nchunk, 256, 0, s>>>(g.lo.p, g.hi.p, off, M->n_inst, bs, stride, 0, M->pz.p, M->pp.p);
   }
   HIP_CHECK(hipGetLastError());
   bpcg_status_kernel<<<1, 64, 0, s>>>(bs, stride, nsys, M->bstat.p);

@@ -1078,41 +1078,65 @@ __global__ void bpcg_init_kernel(size_t n, const double* __restrict__ b, double*
   x[g] = 0.0;
 }
 
-// x += alpha p ; r -= alpha w   (alpha of the element's system; systems with alpha = 0
-// are left untouched, so a stopped system keeps its x and r exactly)
+// The vector updates run over the chunks of the dot products, one workgroup a chunk: thread t
+// keeps column t % NR, so a chunk's system is looked up once, and the update of r also gives
+// the partial sums of r.r.  Ten systems of 9 - 44 elements an edge, eight right-hand sides,
+// FP32 hierarchy: update 56 + 15 us for the dot -> 48, direction 41 -> 23 us; before, every
+// element searched its system.  The solve 20.3 -> 19.5 ms with 20 iterations.
+
 // x += alpha p, r -= alpha w per system (alpha = 0: frozen, untouched); with r32 set,
-// also the FP32 copy of r that an FP32 V-cycle takes as input
-__global__ void bpcg_axpy_kernel(size_t nrow, int nr, const int32_t* __restrict__ off, int nseg,
-                                 const double* __restrict__ bs, int stride, const double* __restrict__ p,
-                                 const double* __restrict__ w, double* __restrict__ x, double* __restrict__ r,
-                                 float* __restrict__ r32) {
-  const size_t g = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
-  if (g >= nrow * nr) return;
-  const int row = static_cast<int>(g / nr), q = static_cast<int>(g % nr);
-  const int sg = nseg > 1 ? seg_of(off, nseg, row) : 0;
-  const double a = bs[B_ALPHA * stride + sg * nr + q];
-  if (a == 0.0) return;
-  x[g] = fmadd(a, p[g], x[g]);
-  const double rv = fmadd(-a, w[g], r[g]);
-  r[g] = rv;
-  if (r32) r32[g] = static_cast<float>(rv);
+// also the FP32 copy of r that an FP32 V-cycle takes as input; partial sums of r.r
+template <int NR>
+__global__ __launch_bounds__(256) void bpcg_axpy_kernel(const int32_t* __restrict__ lo, const int32_t* __restrict__ hi,
+                                                        const int32_t* __restrict__ off, int nseg,
+                                                        const double* __restrict__ bs, int stride,
+                                                        const double* __restrict__ p, const double* __restrict__ w,
+                                                        double* __restrict__ x, double* __restrict__ r,
+                                                        float* __restrict__ r32, double* __restrict__ partial) {
+  static_assert(NR == 1 || NR == 8);
+  __shared__ double lds[4 * NR];
+  const int c = blockIdx.x, q = threadIdx.x % NR;
+  const int sg = nseg > 1 ? seg_of(off, nseg, lo[c]) : 0;
+  const double a = bs[B_ALPHA * stride + sg * NR + q];
+  const size_t end = static_cast<size_t>(hi[c]) * NR;
+  double acc = 0.0;
+#pragma unroll 4
+  for (size_t g = static_cast<size_t>(lo[c]) * NR + threadIdx.x; g < end; g += 256) {
+    double rv = r[g];
+    if (a != 0.0) {
+      x[g] = fmadd(a, p[g], x[g]);
+      rv = fmadd(-a, w[g], rv);
+      r[g] = rv;
+      if (r32) r32[g] = static_cast<float>(rv);
+    }
+    acc = fmadd(rv, rv, acc);
+  }
+#pragma unroll
+  for (int d = NR; d < 64; d <<= 1) acc += __shfl_xor(acc, d, 64);
+  if ((threadIdx.x & 63) < NR) lds[(threadIdx.x >> 6) * NR + q] = acc;
+  __syncthreads();
+  if (threadIdx.x < NR)
+    partial[static_cast<size_t>(c) * NR + q] = ((lds[q] + lds[NR + q]) + lds[2 * NR + q]) + lds[3 * NR + q];
 }
 
 // p = z + beta p  (p = z on the first step or when beta = 0)
-template <class TZ>
-__global__ void bpcg_p_kernel(size_t nrow, int nr, const int32_t* __restrict__ off, int nseg,
-                              const double* __restrict__ bs, int stride, int use_beta, const TZ* __restrict__ z,
-                              double* __restrict__ p) {
-  const size_t g = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
-  if (g >= nrow * nr) return;
-  double v = static_cast<double>(z[g]);
+template <int NR, class TZ>
+__global__ __launch_bounds__(256) void bpcg_p_kernel(const int32_t* __restrict__ lo, const int32_t* __restrict__ hi,
+                                                     const int32_t* __restrict__ off, int nseg,
+                                                     const double* __restrict__ bs, int stride, int use_beta,
+                                                     const TZ* __restrict__ z, double* __restrict__ p) {
+  const int c = blockIdx.x, q = threadIdx.x % NR;
+  double b = 0.0;
   if (use_beta) {
-    const int row = static_cast<int>(g / nr), q = static_cast<int>(g % nr);
-    const int sg = nseg > 1 ? seg_of(off, nseg, row) : 0;
-    const double b = bs[B_BETA * stride + sg * nr + q];
-    if (b != 0.0) v = fmadd(b, p[g], v);
+    const int sg = nseg > 1 ? seg_of(off, nseg, lo[c]) : 0;
+    b = bs[B_BETA * stride + sg * NR + q];
   }
-  p[g] = v;
+  const size_t end = static_cast<size_t>(hi[c]) * NR;
+#pragma unroll 4
+  for (size_t g = static_cast<size_t>(lo[c]) * NR + threadIdx.x; g < end; g += 256) {
+    const double v = static_cast<double>(z[g]);
+    p[g] = b != 0.0 ? fmadd(b, p[g], v) : v;
+  }
 }
 
 // ---------------------------------------------------------------------------
