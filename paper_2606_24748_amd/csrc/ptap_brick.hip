@@ -45,6 +45,7 @@ constexpr int kBatchRows = 64;           // rows of a batch at most
 constexpr int kGroupRows = 128;          // rows of a brick at most
 constexpr int kGroupCand = 1024;         // contributions of a brick at most (their codes lie in LDS)
 constexpr int kPiece = 7;                // P blocks one wave instruction copies (nine lanes a block)
+constexpr int kPieces = kThreads;        // pieces of a batch at most: a wave holds its own ones, a lane each
 constexpr int kBlk = 18;                 // values of a 3x6 block
 constexpr int kLdsP = 50 * 1024;         // LDS for the rows of P: two workgroups stay on a CU
 
@@ -387,15 +388,17 @@ __global__ __launch_bounds__(256) void brick_stage_kernel(Patterns t, const int3
     own[p] = static_cast<uint16_t>(ofs[lower_bound(key, 0, uniq, rows[p])]);
 }
 
-// A batch too large for LDS is cut in two at its middle row (bhead set there); a single row
-// that does not fit ends the attempt.
+// A batch too large for LDS, or of more pieces than the waves hold (scattered rows of one P
+// block each), is cut in two at its middle row (bhead set there); a single row that does not
+// fit ends the attempt.
 __global__ void brick_cut_kernel(int nb, int p_cap, const int32_t* __restrict__ batch_row,
-                                 const int32_t* __restrict__ n_blocks, int32_t* __restrict__ bhead,
+                                 const int32_t* __restrict__ n_blocks, const int32_t* __restrict__ n_pieces,
+                                 int32_t* __restrict__ bhead,
                                  int* __restrict__ cut, int* __restrict__ bad) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= nb) return;
   const int p0 = batch_row[b], p1 = batch_row[b + 1];
-  if (n_blocks[p0] <= p_cap) return;
+  if (n_blocks[p0] <= p_cap && n_pieces[p0] <= kPieces) return;
   if (p1 - p0 < 2) *bad = 1;
   else bhead[(p0 + p1) / 2] = 1;
   *cut = 1;
@@ -630,7 +633,7 @@ __global__ __launch_bounds__(kThreads, 4) void brick_kernel(BrickArgs g, const T
       d[at] = v.b;  // the load was moved back by one
     }
   };
-  int2 pd;  // lane u holds the wave's u-th piece
+  int2 pd;  // lane u holds the wave's u-th piece (kPieces: at most 64 a wave)
   auto piece = [&](int u) {
     return make_int2(__builtin_amdgcn_readlane(pd.x, u), __builtin_amdgcn_readlane(pd.y, u));
   };
@@ -948,7 +951,7 @@ bool brick_symbolic(const bsr_s* A, const bsr_s* P, const bsr_s* C, PtapPlan& pl
   DevBuf<int32_t> n_pieces, n_chunks, batch_row, group_row, group_batch, piece_ptr, batch_chunk, slot_ptr;
   group_row.alloc(static_cast<size_t>(k.ng) + 1);
   group_batch.alloc(static_cast<size_t>(k.ng) + 1);
-  // batches whose rows of P fit LDS: cut in two until they do
+  // batches whose rows of P fit LDS and the waves' registers: cut in two until they do
   k.p_cap = static_cast<int>(kLdsP / (kBlk * acc));
   int64_t total_pieces = 0, chunks = 0;
   for (int round = 0;; ++round) {
@@ -958,8 +961,8 @@ bool brick_symbolic(const bsr_s* A, const bsr_s* P, const bsr_s* C, PtapPlan& pl
     HIP_CHECK(hipMemsetAsync(cut, 0, 2 * sizeof(int), s));
     brick_stage_kernel<true><<<nb, 256, 0, s>>>(t, batch_row.p, rows, k.a_off.p, pos_pieces, pos_blocks,
                                                 pos_end, nullptr, nullptr, nullptr, nullptr);
-    brick_cut_kernel<<<(nb + 255) / 256, 256, 0, s>>>(nb, k.p_cap, batch_row.p, pos_blocks, bhead, cut,
-                                                      bad.p);
+    brick_cut_kernel<<<(nb + 255) / 256, 256, 0, s>>>(nb, k.p_cap, batch_row.p, pos_blocks, pos_pieces, bhead,
+                                                      cut, bad.p);
     HIP_CHECK(hipGetLastError());
     // the next round's batches, and the sizes if this one was the last
     scan32(bhead, bid, used, tmp, s);
