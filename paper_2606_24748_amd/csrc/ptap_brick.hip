@@ -839,7 +839,28 @@ void scan32(const int32_t* in, int32_t* out, int n, DevBuf<char>& tmp, hipStream
   HIP_CHECK(hipcub::DeviceScan::InclusiveSum(tmp.p, bytes, in, out + 1, n, s));
 }
 
-constexpr int kFetch = 6;
+// *out += the sum of n values, in 64 bits
+__global__ __launch_bounds__(256) void sum64_kernel(int n, const int32_t* __restrict__ in,
+                                                    unsigned long long* __restrict__ out) {
+  unsigned long long v = 0;
+  for (int64_t i = blockIdx.x * 256 + static_cast<int>(threadIdx.x); i < n; i += gridDim.x * 256)
+    v += static_cast<unsigned long long>(in[i]);
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+  if ((threadIdx.x & 63) == 0 && v) atomicAdd(out, v);
+}
+
+// *out = the sum of n sizes whose offsets scan32 may not hold; read as two of fetch's values (to64)
+void sum64(const int32_t* in, int n, unsigned long long* out, hipStream_t s) {
+  HIP_CHECK(hipMemsetAsync(out, 0, sizeof(*out), s));
+  if (n > 0) sum64_kernel<<<std::min((n + 255) / 256, 512), 256, 0, s>>>(n, in, out);
+  HIP_CHECK(hipGetLastError());
+}
+int64_t to64(int32_t lo, int32_t hi) {
+  return static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32 | static_cast<uint32_t>(lo));
+}
+
+constexpr int kFetch = 8;
 struct Places {
   const int32_t* p[kFetch];
 };
@@ -901,7 +922,9 @@ bool brick_symbolic(const bsr_s* A, const bsr_s* P, const bsr_s* C, PtapPlan& pl
   auto take = [&]() { return work.p + each * taken++; };
   int32_t *rows = take(), *first = take(), *need_s = take(), *alen_s = take(), *cand_s = take(), *head = take();
   int32_t *need_off = take(), *cand_off = take();
-  DevBuf<unsigned long long> total_d(2);
+  DevBuf<unsigned long long> total_d(3);
+  unsigned long long* const sum_d = total_d.p + 2;
+  const int32_t* const sum_w = reinterpret_cast<const int32_t*>(sum_d);
   DevBuf<int> bad(3 + kFetch);  // bad, cut, most blocks of a batch; what fetch reads
   int* const cut = bad.p + 1;
   int* const got = bad.p + 3;
@@ -975,18 +998,19 @@ bool brick_symbolic(const bsr_s* A, const bsr_s* P, const bsr_s* C, PtapPlan& pl
     HIP_CHECK(hipGetLastError());
     scan32(n_pieces.p, piece_ptr.p, nb, tmp, s);
     scan32(n_chunks.p, batch_chunk.p, nb, tmp, s);
-    const auto h = fetch({bad.p, cut, cut + 1, piece_ptr.p + nb, batch_chunk.p + nb, bid + used}, got, s);
+    sum64(n_pieces.p, nb, sum_d, s);
+    const auto h = fetch({bad.p, cut, cut + 1, batch_chunk.p + nb, bid + used, sum_w, sum_w + 1}, got, s);
     if (h[0]) return false;
     if (!h[1]) {
       k.p_cap = std::max(h[2], 1);
-      total_pieces = h[3];
-      chunks = h[4];
+      chunks = h[3];
+      total_pieces = to64(h[5], h[6]);
       break;
     }
     if (round == 8) return false;
-    nb = h[5];
+    nb = h[4];
   }
-  if (total_pieces == 0) return false;
+  if (total_pieces == 0 || total_pieces > INT32_MAX) return false;
   k.pieces.alloc(static_cast<size_t>(total_pieces) * 2);
   DevBuf<uint16_t> pofs(n_a);
   brick_stage_kernel<false><<<nb, 256, 0, s>>>(t, batch_row.p, rows, k.a_off.p, nullptr, nullptr, nullptr,
@@ -1006,8 +1030,14 @@ bool brick_symbolic(const bsr_s* A, const bsr_s* P, const bsr_s* C, PtapPlan& pl
     HIP_CHECK(hipGetLastError());
   };
   order(std::true_type{}, uint8_t{});
+  // a chunk is padded to 16 times its longest list, so the tables can outgrow the pair list
+  // (rows of many A blocks and few A P blocks) and 32 bits
   scan32(chunk_len.p, k.chunk_off.p, static_cast<int>(chunks), tmp, s);
-  k.ell.alloc(std::max<int64_t>(fetch({k.chunk_off.p + chunks}, got, s)[0], 1));
+  sum64(chunk_len.p, static_cast<int>(chunks), sum_d, s);
+  const auto h1 = fetch({sum_w, sum_w + 1}, got, s);
+  const int64_t n_ell = to64(h1[0], h1[1]);
+  if (n_ell > INT32_MAX) return false;
+  k.ell.alloc(std::max<int64_t>(n_ell, 1));
   if (pr.width == 1) order(std::false_type{}, uint8_t{});
   else if (pr.width == 2) order(std::false_type{}, uint16_t{});
   else order(std::false_type{}, uint32_t{});
