@@ -1,0 +1,187 @@
+// Device memory of the library: the caller's allocator, the blocks kept between setups, and
+// the owning buffer.  Host code only (no kernel), over the HIP calls of hip_runtime_api.h.
+#pragma once
+
+#include <hip/hip_runtime_api.h>
+
+#include <cstddef>
+#include <cstdint>
+#include <map>
+#include <mutex>
+#include <string>
+#include <utility>
+
+#include "errors.hpp"
+
+namespace blk {
+
+// ---------------------------------------------------------------------------
+// Device allocator: hipMalloc/hipFree, or the caller's pair of routines
+// ---------------------------------------------------------------------------
+struct DeviceAllocator {
+  blkamg_alloc_fn alloc_fn = nullptr;  // NULL: hipMalloc / hipFree
+  blkamg_free_fn free_fn = nullptr;
+  void* ctx = nullptr;
+};
+inline std::mutex& allocator_mutex() {
+  static std::mutex m;
+  return m;
+}
+inline DeviceAllocator& allocator_slot() {
+  static DeviceAllocator a;
+  return a;
+}
+inline DeviceAllocator current_allocator() {
+  std::lock_guard<std::mutex> g(allocator_mutex());
+  return allocator_slot();
+}
+constexpr uintptr_t kDevAlign = 256;
+
+// Freed blocks, kept for the setups and plans that come next.  A setup makes and frees some
+// 200 buffers; hipMalloc and hipFree take microseconds for a small one and 0.3 - 0.7 ms for
+// 50 - 130 MB, 9 ms of the 18 ms of an FP64 setup of a 40^3-element mesh.  With kept blocks
+// that setup takes 12.4 ms, an FP32 one 21 instead of 30, 64^3 36 instead of 47 (FP64).
+// Bounded by kHeld (1.5 % of the device's memory; a bound of 1 GiB left 64^3 at 43 ms), given
+// back when the last buffer of the library is freed and when memory runs out.  Blocks are
+// handed out inside an AllocScope only (calls that wait for their stream anyway, so never
+// under capture), after the device has been idle once since the block came back, as it is
+// after a hipFree: no stream, copy or host write can meet its former use.  A block serves
+// requests of at least 7/8 of its size (any up to 64 KB).
+class BlockCache {
+ public:
+  static BlockCache& get() {
+    static BlockCache* c = new BlockCache;  // outlives every buffer
+    return *c;
+  }
+  // NULL when there is no memory; cap: the size to hand back
+  void* make(size_t bytes, bool reuse, int& dev, size_t& cap) {
+    (void)hipGetDevice(&dev);
+    std::lock_guard<std::mutex> g(m_);
+    if (reuse) {
+      const auto it = free_.lower_bound({dev, bytes});
+      if (it != free_.end() && it->first.first == dev &&
+          (it->first.second <= kAny || it->first.second - it->first.second / 8 <= bytes) &&
+          (!unsynced_ || hipDeviceSynchronize() == hipSuccess)) {
+        unsynced_ = false;
+        void* p = it->second;
+        cap = it->first.second;
+        held_ -= cap;
+        ++live_;
+        free_.erase(it);
+        return p;
+      }
+    }
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      if (free_.empty()) return nullptr;
+      flush();
+      if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+      }
+    }
+    cap = bytes;
+    ++live_;
+    return p;
+  }
+  void give(void* p, int dev, size_t cap) noexcept {
+    std::lock_guard<std::mutex> g(m_);
+    --live_;
+    bool kept = false;
+    if (live_ > 0 && held_ + cap <= kHeld) {
+      try {
+        free_.emplace(std::make_pair(dev, cap), p);
+        kept = unsynced_ = true;
+        held_ += cap;
+      } catch (...) {
+      }
+    }
+    if (!kept) (void)hipFree(p);
+    if (live_ == 0) flush();
+  }
+
+ private:
+  static constexpr size_t kAny = 64 * 1024, kHeld = size_t{4} << 30;
+  void flush() noexcept {
+    for (const auto& f : free_) (void)hipFree(f.second);
+    free_.clear();
+    held_ = 0;
+  }
+  std::mutex m_;
+  std::multimap<std::pair<int, size_t>, void*> free_;  // by device and size
+  size_t held_ = 0, live_ = 0;
+  bool unsynced_ = false;
+};
+
+// While one is open, this thread's allocations take kept blocks.
+class AllocScope {
+ public:
+  AllocScope() { ++depth(); }
+  ~AllocScope() { --depth(); }
+  AllocScope(const AllocScope&) = delete;
+  AllocScope& operator=(const AllocScope&) = delete;
+  static int& depth() {
+    thread_local int d = 0;
+    return d;
+  }
+};
+
+// ---------------------------------------------------------------------------
+// Device buffer (owning, freed on destruction by the routine that allocated it)
+// ---------------------------------------------------------------------------
+template <class T>
+struct DevBuf {
+  T* p = nullptr;
+  size_t n = 0;
+  DeviceAllocator by;
+  int dev = 0;     // hipMalloc: device and size of the block
+  size_t cap = 0;
+  DevBuf() = default;
+  explicit DevBuf(size_t count) { alloc(count); }
+  DevBuf(const DevBuf&) = delete;
+  DevBuf& operator=(const DevBuf&) = delete;
+  DevBuf(DevBuf&& o) noexcept : p(o.p), n(o.n), by(o.by), dev(o.dev), cap(o.cap) { o.p = nullptr; o.n = 0; }
+  DevBuf& operator=(DevBuf&& o) noexcept {
+    if (this != &o) { release(); p = o.p; n = o.n; by = o.by; dev = o.dev; cap = o.cap; o.p = nullptr; o.n = 0; }
+    return *this;
+  }
+  ~DevBuf() { release(); }
+  void alloc(size_t count) {
+    release();
+    if (count == 0) return;
+    const size_t bytes = count * sizeof(T);
+    const DeviceAllocator a = current_allocator();
+    void* q = nullptr;
+    if (a.alloc_fn) {
+      q = a.alloc_fn(bytes, a.ctx);
+      if (q == nullptr) fail(BLKAMG_ENOMEM, "the caller's allocator returned NULL for " + std::to_string(bytes) + " bytes");
+      if (reinterpret_cast<uintptr_t>(q) % kDevAlign != 0) {
+        a.free_fn(q, bytes, a.ctx);
+        fail(BLKAMG_EINVAL, "the caller's allocator returned a pointer not aligned to 256 bytes");
+      }
+    } else {
+      q = BlockCache::get().make(bytes, AllocScope::depth() > 0, dev, cap);
+      if (q == nullptr) fail(BLKAMG_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+    }
+    p = static_cast<T*>(q);
+    n = count;
+    by = a;
+  }
+  void release() {
+    if (p) {
+      if (by.free_fn) {
+        // as hipFree does: nothing queued may still use the buffer when it is handed back
+        (void)hipDeviceSynchronize();
+        by.free_fn(p, n * sizeof(T), by.ctx);
+      } else {
+        BlockCache::get().give(p, dev, cap);
+      }
+    }
+    p = nullptr;
+    n = 0;
+  }
+  size_t bytes() const { return n * sizeof(T); }
+};
+
+}  // namespace blk
