@@ -8,6 +8,7 @@
 #include <cstdint>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <utility>
 
@@ -44,7 +45,7 @@ constexpr uintptr_t kDevAlign = 256;
 // Bounded by kHeld (1.5 % of the device's memory; a bound of 1 GiB left 64^3 at 43 ms), given
 // back when the last buffer of the library is freed and when memory runs out.  Blocks are
 // handed out inside an AllocScope only (calls that wait for their stream anyway, so never
-// under capture), after the device has been idle once since the block came back, as it is
+// under capture), after the block's device has been idle once since the block came back, as it is
 // after a hipFree: no stream, copy or host write can meet its former use.  A block serves
 // requests of at least 7/8 of its size (any up to 64 KB).
 class BlockCache {
@@ -61,8 +62,7 @@ class BlockCache {
       const auto it = free_.lower_bound({dev, bytes});
       if (it != free_.end() && it->first.first == dev &&
           (it->first.second <= kAny || it->first.second - it->first.second / 8 <= bytes) &&
-          (!unsynced_ || hipDeviceSynchronize() == hipSuccess)) {
-        unsynced_ = false;
+          synced(dev)) {
         void* p = it->second;
         cap = it->first.second;
         held_ -= cap;
@@ -91,8 +91,9 @@ class BlockCache {
     bool kept = false;
     if (live_ > 0 && held_ + cap <= kHeld) {
       try {
+        unsynced_.insert(dev);
         free_.emplace(std::make_pair(dev, cap), p);
-        kept = unsynced_ = true;
+        kept = true;
         held_ += cap;
       } catch (...) {
       }
@@ -108,10 +109,20 @@ class BlockCache {
     free_.clear();
     held_ = 0;
   }
+  // the current device `dev` has been idle since its last block came back
+  bool synced(int dev) {
+    if (unsynced_.count(dev) == 0) return true;
+    if (hipDeviceSynchronize() != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    unsynced_.erase(dev);
+    return true;
+  }
   std::mutex m_;
   std::multimap<std::pair<int, size_t>, void*> free_;  // by device and size
   size_t held_ = 0, live_ = 0;
-  bool unsynced_ = false;
+  std::set<int> unsynced_;  // devices with blocks that came back since their last wait
 };
 
 // While one is open, this thread's allocations take kept blocks.

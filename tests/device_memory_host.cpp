@@ -1,0 +1,107 @@
+// Host test of the device buffers: the library's header over a model of two devices, in which
+// memory has a size, work is in flight until its device is waited for, and hipFree waits.
+// The first argument names the scenario; exit status 0 when it holds.
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <set>
+#include <string>
+
+#include "../paper_2606_24748_amd/csrc/device_memory.hpp"
+
+namespace {
+struct Model {
+  int current = 0;
+  size_t free_bytes[2] = {size_t{64} << 30, size_t{64} << 30};
+  std::map<void*, std::pair<int, size_t>> owned;  // device and size of every block
+  std::set<void*> in_use[2];                      // blocks that queued work of the device still uses
+  int waits[2] = {0, 0}, mallocs = 0, frees = 0;
+  bool fail_waits = false;  // as while a stream is captured
+  uintptr_t next = 4096;
+} model;
+
+void wait(int d) {
+  ++model.waits[d];
+  model.in_use[d].clear();
+}
+}  // namespace
+
+extern "C" {
+hipError_t hipGetDevice(int* d) { *d = model.current; return hipSuccess; }
+hipError_t hipSetDevice(int d) { model.current = d; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "model"; }
+hipError_t hipDeviceSynchronize() {
+  if (model.fail_waits) return hipErrorStreamCaptureUnsupported;
+  wait(model.current);
+  return hipSuccess;
+}
+hipError_t hipMalloc(void** p, size_t bytes) {
+  size_t& left = model.free_bytes[model.current];
+  if (bytes > left) return hipErrorOutOfMemory;
+  left -= bytes;
+  *p = reinterpret_cast<void*>(model.next);
+  model.next += (bytes + 4095) / 4096 * 4096;
+  model.owned[*p] = {model.current, bytes};
+  ++model.mallocs;
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  const auto it = model.owned.find(p);
+  if (it == model.owned.end()) std::abort();
+  wait(it->second.first);
+  model.free_bytes[it->second.first] += it->second.second;
+  model.owned.erase(it);
+  ++model.frees;
+  return hipSuccess;
+}
+}
+
+namespace blk {
+void set_last_error(const std::string&) {}
+}  // namespace blk
+
+using blk::AllocScope;
+using blk::DevBuf;
+
+#define CHECK(c)                                                       \
+  do {                                                                 \
+    if (!(c)) {                                                        \
+      std::printf("line %d: %s does not hold\n", __LINE__, #c);        \
+      return 1;                                                        \
+    }                                                                  \
+  } while (0)
+
+namespace {
+void queue(int d, const DevBuf<char>& b) { model.in_use[d].insert(b.p); }
+bool busy(const DevBuf<char>& b) { return model.in_use[0].count(b.p) || model.in_use[1].count(b.p); }
+
+// A block of each device comes back with work in flight; waiting for one device must not pass
+// for waiting for the other.
+int two_devices() {
+  DevBuf<char> alive(256);
+  for (int d = 0; d < 2; ++d) {
+    AllocScope scope;
+    model.current = d;
+    DevBuf<char> b(1 << 20);
+    queue(d, b);
+  }
+  DevBuf<char> again[2];
+  for (int d = 0; d < 2; ++d) {
+    AllocScope scope;
+    model.current = d;
+    const int before = model.mallocs;
+    again[d].alloc(1 << 20);
+    CHECK(model.mallocs == before);  // the kept block
+    CHECK(model.owned.at(again[d].p).first == d);
+    CHECK(!busy(again[d]));
+  }
+  return 0;
+}
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::map<std::string, int (*)()> all{{"two_devices", two_devices}};
+  const auto it = argc == 2 ? all.find(argv[1]) : all.end();
+  return it == all.end() ? 2 : it->second();
+}
