@@ -125,7 +125,9 @@ int bsr_create(int32_t nbr, int32_t nbc, int32_t bs_r, int32_t bs_c, int64_t nnz
                const int32_t* d_rowptr, const int32_t* d_colidx, void* d_val,
                int dtype, void* stream, bsr_t* out);
 /* Free the handle and everything it owns (caches; for library-created matrices
- * also the arrays).  NULL is accepted. */
+ * also the arrays).  NULL is accepted.  As with hipFree, a handle that owns device
+ * memory waits for the device first (so do coo_plan_destroy, fe_ebe_plan_destroy and
+ * amg_destroy): borrowed arrays may then be freed. */
 int bsr_destroy(bsr_t A);
 /* Declare that the values changed: bumps the value-state stamp that gates the
  * cached transpose and the prolongator-side data of the Galerkin product

@@ -1764,6 +1764,7 @@ int amg_setup_batched(bsr_t A0, int32_t n_inst, const int32_t* h_inst_row0, cons
 int amg_destroy(amg_t M) {
   BLK_API_BEGIN
   if (M) (void)hipDeviceSynchronize();
+  FreeScope scope;
   delete M;
   BLK_API_END
 }

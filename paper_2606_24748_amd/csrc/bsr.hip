@@ -487,6 +487,7 @@ int bsr_create(int32_t nbr, int32_t nbc, int32_t bs_r, int32_t bs_c, int64_t nnz
 
 int bsr_destroy(bsr_t A) {
   BLK_API_BEGIN
+  FreeScope scope;
   delete A;
   BLK_API_END
 }

@@ -404,6 +404,7 @@ int coo_plan_create(int32_t nbr, int32_t nbc, int32_t bs_r, int32_t bs_c, int64_
 
 int coo_plan_destroy(coo_plan_t plan) {
   BLK_API_BEGIN
+  FreeScope scope;
   delete plan;
   BLK_API_END
 }

@@ -6,6 +6,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <exception>
 #include <map>
 #include <mutex>
 #include <set>
@@ -37,6 +38,17 @@ inline DeviceAllocator current_allocator() {
   return allocator_slot();
 }
 constexpr uintptr_t kDevAlign = 256;
+
+// Waits for all work of a device, current or not; false where that is not possible (capture).
+inline bool wait_for_device(int dev) {
+  int cur = dev;
+  (void)hipGetDevice(&cur);
+  if (cur != dev) (void)hipSetDevice(dev);
+  const bool ok = hipDeviceSynchronize() == hipSuccess;
+  if (!ok) (void)hipGetLastError();
+  if (cur != dev) (void)hipSetDevice(cur);
+  return ok;
+}
 
 // Freed blocks, kept for the setups and plans that come next.  A setup makes and frees some
 // 200 buffers; hipMalloc and hipFree take microseconds for a small one and 0.3 - 0.7 ms for
@@ -85,13 +97,14 @@ class BlockCache {
     ++live_;
     return p;
   }
-  void give(void* p, int dev, size_t cap) noexcept {
+  // waited: no queued work uses the block any more
+  void give(void* p, int dev, size_t cap, bool waited) noexcept {
     std::lock_guard<std::mutex> g(m_);
     --live_;
     bool kept = false;
     if (live_ > 0 && held_ + cap <= kHeld) {
       try {
-        unsynced_.insert(dev);
+        if (!waited) unsynced_.insert(dev);
         free_.emplace(std::make_pair(dev, cap), p);
         kept = true;
         held_ += cap;
@@ -112,10 +125,7 @@ class BlockCache {
   // the current device `dev` has been idle since its last block came back
   bool synced(int dev) {
     if (unsynced_.count(dev) == 0) return true;
-    if (hipDeviceSynchronize() != hipSuccess) {
-      (void)hipGetLastError();
-      return false;
-    }
+    if (!wait_for_device(dev)) return false;
     unsynced_.erase(dev);
     return true;
   }
@@ -125,15 +135,50 @@ class BlockCache {
   std::set<int> unsynced_;  // devices with blocks that came back since their last wait
 };
 
-// While one is open, this thread's allocations take kept blocks.
+// While one is open, this thread's allocations take kept blocks, and released buffers go back
+// without a wait: for calls that wait for their stream before they return.  One that is left
+// by an exception waits for the device instead, so that a call that failed has nothing queued
+// on the caller's arrays.
 class AllocScope {
  public:
-  AllocScope() { ++depth(); }
-  ~AllocScope() { --depth(); }
+  AllocScope() : thrown_(std::uncaught_exceptions()) { ++depth(); }
+  ~AllocScope() {
+    int dev = 0;
+    if (--depth() == 0 && std::uncaught_exceptions() > thrown_ && hipGetDevice(&dev) == hipSuccess) wait_for_device(dev);
+  }
   AllocScope(const AllocScope&) = delete;
   AllocScope& operator=(const AllocScope&) = delete;
   static int& depth() {
     thread_local int d = 0;
+    return d;
+  }
+
+ private:
+  int thrown_;
+};
+
+// A buffer released outside an AllocScope waits for its device, as hipFree does: callers free
+// borrowed arrays once the handle is gone.  While a FreeScope is open, this thread does so at
+// the first buffer of a device only (the destruction of a handle, which queues nothing).
+class FreeScope {
+ public:
+  FreeScope() { if (depth()++ == 0) waited() = -1; }
+  ~FreeScope() { --depth(); }
+  FreeScope(const FreeScope&) = delete;
+  FreeScope& operator=(const FreeScope&) = delete;
+  static bool wait(int dev) {
+    if (depth() == 0) return AllocScope::depth() == 0 && wait_for_device(dev);
+    if (waited() != dev && wait_for_device(dev)) waited() = dev;
+    return waited() == dev;
+  }
+
+ private:
+  static int& depth() {
+    thread_local int d = 0;
+    return d;
+  }
+  static int& waited() {
+    thread_local int d = -1;
     return d;
   }
 };
@@ -186,7 +231,7 @@ struct DevBuf {
         (void)hipDeviceSynchronize();
         by.free_fn(p, n * sizeof(T), by.ctx);
       } else {
-        BlockCache::get().give(p, dev, cap);
+        BlockCache::get().give(p, dev, cap, FreeScope::wait(dev));
       }
     }
     p = nullptr;

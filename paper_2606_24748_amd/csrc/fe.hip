@@ -383,6 +383,7 @@ int fe_ebe_plan_info(fe_plan_t P, int32_t* n_colors, int64_t* slot_bytes) {
 
 int fe_ebe_plan_destroy(fe_plan_t P) {
   BLK_API_BEGIN
+  FreeScope scope;
   delete P;
   BLK_API_END
 }

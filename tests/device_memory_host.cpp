@@ -98,10 +98,75 @@ int two_devices() {
   }
   return 0;
 }
+
+// Outside a setup a released buffer waits for its device, current or not, as hipFree does ...
+int release_waits() {
+  DevBuf<char> alive(256), far(4096), near(4096);
+  model.current = 1;
+  far.alloc(4096);
+  model.current = 0;
+  queue(0, near);
+  queue(1, far);
+  far.release();
+  CHECK(model.in_use[1].empty() && model.in_use[0].size() == 1 && model.current == 0);
+  near.release();
+  CHECK(model.in_use[0].empty());
+  return 0;
+}
+
+// ... a handle's buffers together once, and so does a setup that fails; one that does not fail
+// waits for its own stream by itself.
+int scopes_wait() {
+  DevBuf<char> alive(256), many[5];
+  for (auto& b : many) queue(0, (b.alloc(4096), b));
+  {
+    blk::FreeScope scope;
+    for (auto& b : many) b.release();
+  }
+  CHECK(model.in_use[0].empty() && model.waits[0] == 1);
+  for (const bool fails : {false, true}) {
+    DevBuf<char> caller(512);
+    try {
+      AllocScope outer;
+      {
+        AllocScope inner;
+        DevBuf<char> b(100 << 10);
+      }
+      queue(0, caller);
+      if (fails) blk::fail(BLKAMG_EINVAL, "as a setup would");
+    } catch (const blk::Error&) {
+    }
+    CHECK(busy(caller) == !fails);
+    model.in_use[0].clear();
+  }
+  return 0;
+}
+
+// A wait that is refused (capture) does not count as one.
+int refused_waits() {
+  DevBuf<char> alive(256), b(1 << 20);
+  queue(0, b);
+  void* const p = b.p;
+  model.fail_waits = true;
+  b.release();
+  {
+    AllocScope scope;
+    b.alloc(1 << 20);
+    CHECK(b.p != p);  // not handed out
+  }
+  model.fail_waits = false;
+  AllocScope scope;
+  DevBuf<char> c(1 << 20);
+  CHECK(c.p == p && !busy(c));
+  return 0;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
-  const std::map<std::string, int (*)()> all{{"two_devices", two_devices}};
+  const std::map<std::string, int (*)()> all{{"two_devices", two_devices},
+                                                {"release_waits", release_waits},
+                                                {"scopes_wait", scopes_wait},
+                                                {"refused_waits", refused_waits}};
   const auto it = argc == 2 ? all.find(argv[1]) : all.end();
   return it == all.end() ? 2 : it->second();
 }
