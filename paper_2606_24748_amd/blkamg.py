@@ -73,6 +73,7 @@ _SIG = {
     "blkamg_last_error": (C.c_char_p, []),
     "blkamg_version": (C.c_int, []),
     "blkamg_set_allocator": (C.c_int, [_p, _p, _p]),
+    "blkamg_trim": (C.c_int, []),
     "bsr_create": (C.c_int, [_i32, _i32, _i32, _i32, _i64, _p, _p, _p, C.c_int, _p, C.POINTER(_p)]),
     "bsr_destroy": (C.c_int, [_p]),
     "bsr_mark_modified": (C.c_int, [_p]),
@@ -726,6 +727,11 @@ def blkamg_set_allocator(alloc_fn=None, free_fn=None, ctx=None):
     _check(_lib.blkamg_set_allocator(C.cast(a, _p) if a else None, C.cast(f, _p) if f else None, ctx),
            "blkamg_set_allocator")
     _allocator_keep.append((a, f))
+
+
+def blkamg_trim():
+    """Free the device blocks that the library keeps for its next setups."""
+    _check(_lib.blkamg_trim(), "blkamg_trim")
 
 
 def use_torch_allocator(enable=True):

@@ -440,6 +440,13 @@ int blkamg_set_allocator(blkamg_alloc_fn alloc_fn, blkamg_free_fn free_fn, void*
   a.alloc_fn = alloc_fn;
   a.free_fn = free_fn;
   a.ctx = alloc_fn ? ctx : nullptr;
+  if (alloc_fn) BlockCache::get().trim();
+  BLK_API_END
+}
+
+int blkamg_trim(void) {
+  BLK_API_BEGIN
+  BlockCache::get().trim();
   BLK_API_END
 }
 

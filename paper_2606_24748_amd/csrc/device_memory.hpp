@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 #include <exception>
@@ -54,11 +55,12 @@ inline bool wait_for_device(int dev) {
 // 200 buffers; hipMalloc and hipFree take microseconds for a small one and 0.3 - 0.7 ms for
 // 50 - 130 MB, 9 ms of the 18 ms of an FP64 setup of a 40^3-element mesh.  With kept blocks
 // that setup takes 12.4 ms, an FP32 one 21 instead of 30, 64^3 36 instead of 47 (FP64).
-// Bounded by kHeld (1.5 % of the device's memory; a bound of 1 GiB left 64^3 at 43 ms), given
-// back when the last buffer of the library is freed and when memory runs out.  Blocks are
-// handed out inside an AllocScope only (calls that wait for their stream anyway, so never
-// under capture), after the block's device has been idle once since the block came back, as it is
-// after a hipFree: no stream, copy or host write can meet its former use.  A block serves
+// Bounded per device by kHeld (a bound of 1 GiB left 64^3 at 43 ms) and a 64th of its memory.
+// Given back when the last buffer of the library is freed, when hipMalloc or the caller's
+// allocator has no memory left, when the caller sets an allocator, and by blkamg_trim.  Blocks
+// are handed out inside an AllocScope only (calls that wait for their stream anyway, so never
+// under capture), after the block's device has been idle once since the block came back, as it
+// is after a hipFree: no stream, copy or host write can meet its former use.  A block serves
 // requests of at least 7/8 of its size (any up to 64 KB).
 class BlockCache {
  public:
@@ -77,7 +79,7 @@ class BlockCache {
           synced(dev)) {
         void* p = it->second;
         cap = it->first.second;
-        held_ -= cap;
+        at_[dev].held -= cap;
         ++live_;
         free_.erase(it);
         return p;
@@ -86,8 +88,7 @@ class BlockCache {
     void* p = nullptr;
     if (hipMalloc(&p, bytes) != hipSuccess) {
       (void)hipGetLastError();
-      if (free_.empty()) return nullptr;
-      flush();
+      if (!flush()) return nullptr;
       if (hipMalloc(&p, bytes) != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
@@ -102,37 +103,53 @@ class BlockCache {
     std::lock_guard<std::mutex> g(m_);
     --live_;
     bool kept = false;
-    if (live_ > 0 && held_ + cap <= kHeld) {
-      try {
-        if (!waited) unsynced_.insert(dev);
+    try {
+      if (live_ > 0 && cap <= room(dev)) {
         free_.emplace(std::make_pair(dev, cap), p);
         kept = true;
-        held_ += cap;
-      } catch (...) {
+        at_[dev].held += cap;
+        if (!waited) at_[dev].unsynced = true;
       }
+    } catch (...) {
     }
     if (!kept) (void)hipFree(p);
     if (live_ == 0) flush();
   }
+  // Gives the kept blocks back; false if there were none.
+  bool trim() noexcept {
+    std::lock_guard<std::mutex> g(m_);
+    return flush();
+  }
 
  private:
   static constexpr size_t kAny = 64 * 1024, kHeld = size_t{4} << 30;
-  void flush() noexcept {
+  struct Device {
+    size_t held = 0, most = 0;
+    bool unsynced = false;  // blocks came back since the last wait
+  };
+  size_t room(int dev) {
+    Device& d = at_[dev];
+    size_t total = 0;
+    if (d.most == 0 && hipDeviceTotalMem(&total, dev) == hipSuccess) d.most = std::min(kHeld, total / 64);
+    return d.most - std::min(d.held, d.most);
+  }
+  bool flush() noexcept {
+    if (free_.empty()) return false;
     for (const auto& f : free_) (void)hipFree(f.second);
     free_.clear();
-    held_ = 0;
+    for (auto& d : at_) d.second.held = 0;
+    return true;
   }
   // the current device `dev` has been idle since its last block came back
   bool synced(int dev) {
-    if (unsynced_.count(dev) == 0) return true;
-    if (!wait_for_device(dev)) return false;
-    unsynced_.erase(dev);
-    return true;
+    Device& d = at_[dev];
+    if (d.unsynced) d.unsynced = !wait_for_device(dev);
+    return !d.unsynced;
   }
   std::mutex m_;
   std::multimap<std::pair<int, size_t>, void*> free_;  // by device and size
-  size_t held_ = 0, live_ = 0;
-  std::set<int> unsynced_;  // devices with blocks that came back since their last wait
+  std::map<int, Device> at_;
+  size_t live_ = 0;
 };
 
 // While one is open, this thread's allocations take kept blocks, and released buffers go back
@@ -211,6 +228,7 @@ struct DevBuf {
     void* q = nullptr;
     if (a.alloc_fn) {
       q = a.alloc_fn(bytes, a.ctx);
+      if (q == nullptr && BlockCache::get().trim()) q = a.alloc_fn(bytes, a.ctx);
       if (q == nullptr) fail(BLKAMG_ENOMEM, "the caller's allocator returned NULL for " + std::to_string(bytes) + " bytes");
       if (reinterpret_cast<uintptr_t>(q) % kDevAlign != 0) {
         a.free_fn(q, bytes, a.ctx);

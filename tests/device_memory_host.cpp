@@ -29,6 +29,7 @@ void wait(int d) {
 extern "C" {
 hipError_t hipGetDevice(int* d) { *d = model.current; return hipSuccess; }
 hipError_t hipSetDevice(int d) { model.current = d; return hipSuccess; }
+hipError_t hipDeviceTotalMem(size_t* bytes, int) { *bytes = size_t{64} << 30; return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "model"; }
 hipError_t hipDeviceSynchronize() {
@@ -160,13 +161,77 @@ int refused_waits() {
   CHECK(c.p == p && !busy(c));
   return 0;
 }
+
+size_t used() {
+  size_t sum = 0;
+  for (const auto& b : model.owned) sum += b.second.second;
+  return sum;
+}
+
+// Kept blocks: a 64th of the device's memory at most, for requests of at least 7/8 of their
+// size, and none once the last buffer is gone.
+int bound() {
+  constexpr size_t kMiB = size_t{1} << 20;
+  {
+    DevBuf<char> alive(256);
+    {
+      DevBuf<char> a(600 * kMiB), b(600 * kMiB);
+    }
+    CHECK(used() == 256 + 600 * kMiB);
+    AllocScope scope;
+    int before = model.mallocs;
+    DevBuf<char> small(524 * kMiB);
+    CHECK(model.mallocs == before + 1);
+    DevBuf<char> fits(526 * kMiB);
+    CHECK(model.mallocs == before + 1 && fits.cap == 600 * kMiB);
+  }
+  CHECK(model.owned.empty());
+  return 0;
+}
+
+void* caller_alloc(size_t bytes, void*) {
+  void* p = nullptr;
+  return hipMalloc(&p, bytes) == hipSuccess ? p : nullptr;
+}
+void caller_free(void* p, size_t, void*) { (void)hipFree(p); }
+
+// Kept blocks go back when hipMalloc or the caller's allocator finds no memory, or on request.
+int given_back() {
+  constexpr size_t kGiB = size_t{1} << 30;
+  DevBuf<char> alive(256);
+  for (int round = 0; round < 3; ++round) {
+    DevBuf<char> held(kGiB);
+    held.release();
+    CHECK(used() == 256 + kGiB);
+    if (round == 2) {
+      CHECK(blk::BlockCache::get().trim() && !blk::BlockCache::get().trim());
+    } else {
+      if (round == 1) blk::allocator_slot() = {caller_alloc, caller_free, nullptr};
+      DevBuf<char> rest(63 * kGiB + kGiB / 2);
+      blk::allocator_slot() = {};
+      bool refused = false;
+      try {
+        DevBuf<char> more(kGiB);
+      } catch (const blk::Error& e) {
+        refused = e.code == BLKAMG_ENOMEM;
+      }
+      CHECK(refused);
+      rest.release();
+      blk::BlockCache::get().trim();
+    }
+    CHECK(used() == 256);
+  }
+  return 0;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, int (*)()> all{{"two_devices", two_devices},
                                                 {"release_waits", release_waits},
                                                 {"scopes_wait", scopes_wait},
-                                                {"refused_waits", refused_waits}};
+                                                {"refused_waits", refused_waits},
+                                                {"bound", bound},
+                                                {"given_back", given_back}};
   const auto it = argc == 2 ? all.find(argv[1]) : all.end();
   return it == all.end() ? 2 : it->second();
 }
