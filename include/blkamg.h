@@ -30,7 +30,7 @@
  *   unchanged, for the lifetime of every handle that refers to them.
  * - The library allocates its own device memory (plans, caches, library-owned
  *   matrices, hierarchy work vectors) with hipMalloc at create/setup time, and keeps
- *   blocks that it frees for the next setups (blkamg_trim gives them back); the
+ *   blocks that it frees for its next ones (blkamg_trim gives them back); the
  *   hot calls (spmv, ptap_numeric, coo_assemble_blocked, vcycle_apply, pcg_solve
  *   after its first call on a hierarchy) allocate nothing.
  */
@@ -102,8 +102,8 @@ int blkamg_version(void);
 typedef void* (*blkamg_alloc_fn)(size_t bytes, void* ctx);
 typedef void (*blkamg_free_fn)(void* ptr, size_t bytes, void* ctx);
 int blkamg_set_allocator(blkamg_alloc_fn alloc_fn, blkamg_free_fn free_fn, void* ctx);
-/* Give device memory back.  With the default allocator, freed buffers are kept for the
- * setups and plans that come next: at most 4 GiB and a 64th of the device's memory on
+/* Give device memory back.  With the default allocator, freed buffers are kept for those
+ * that the library allocates next: at most 4 GiB and a 64th of the device's memory on
  * each device, until the last buffer of the library is freed, hipMalloc or the caller's
  * allocator runs out of memory, or an allocator is set.  This call frees them at once,
  * for other users of the device's memory.  Any thread, at any time but during a capture;

@@ -57,22 +57,23 @@ inline bool wait_for_device(int dev) {
 // that setup takes 12.4 ms, an FP32 one 21 instead of 30, 64^3 36 instead of 47 (FP64).
 // Bounded per device by kHeld (a bound of 1 GiB left 64^3 at 43 ms) and a 64th of its memory.
 // Given back when the last buffer of the library is freed, when hipMalloc or the caller's
-// allocator has no memory left, when the caller sets an allocator, and by blkamg_trim.  Blocks
-// are handed out inside an AllocScope only (calls that wait for their stream anyway, so never
-// under capture), after the block's device has been idle once since the block came back, as it
-// is after a hipFree: no stream, copy or host write can meet its former use.  A block serves
-// requests of at least 7/8 of its size (any up to 64 KB).
+// allocator has no memory left, when the caller sets an allocator, and by blkamg_trim.  A block
+// is handed out after its device has been idle once since it came back, as it is after a
+// hipFree: no stream, copy or host write can meet its former use.  An AllocScope (calls that
+// wait for their stream anyway, so never under capture) waits for that; other calls take kept
+// blocks only when there is nothing to wait for, so that what they free does not pile up.  A
+// block serves requests of at least 7/8 of its size (any up to 64 KB).
 class BlockCache {
  public:
   static BlockCache& get() {
     static BlockCache* c = new BlockCache;  // outlives every buffer
     return *c;
   }
-  // NULL when there is no memory; cap: the size to hand back
-  void* make(size_t bytes, bool reuse, int& dev, size_t& cap) {
+  // NULL when there is no memory; may_wait: in an AllocScope; cap: the size to hand back
+  void* make(size_t bytes, bool may_wait, int& dev, size_t& cap) {
     (void)hipGetDevice(&dev);
     std::lock_guard<std::mutex> g(m_);
-    if (reuse) {
+    if (may_wait || !at_[dev].unsynced) {
       const auto it = free_.lower_bound({dev, bytes});
       if (it != free_.end() && it->first.first == dev &&
           (it->first.second <= kAny || it->first.second - it->first.second / 8 <= bytes) &&
@@ -115,6 +116,16 @@ class BlockCache {
     if (!kept) (void)hipFree(p);
     if (live_ == 0) flush();
   }
+  // The end of an AllocScope: what it gave back may be handed out from now on (failed: the
+  // caller's arrays are out of use too).
+  void settle(bool failed) noexcept {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return;
+    std::lock_guard<std::mutex> g(m_);
+    const auto d = at_.find(dev);
+    const bool unsynced = d != at_.end() && d->second.unsynced;
+    if ((failed || unsynced) && wait_for_device(dev) && unsynced) d->second.unsynced = false;
+  }
   // Gives the kept blocks back; false if there were none.
   bool trim() noexcept {
     std::lock_guard<std::mutex> g(m_);
@@ -152,16 +163,15 @@ class BlockCache {
   size_t live_ = 0;
 };
 
-// While one is open, this thread's allocations take kept blocks, and released buffers go back
-// without a wait: for calls that wait for their stream before they return.  One that is left
-// by an exception waits for the device instead, so that a call that failed has nothing queued
-// on the caller's arrays.
+// While one is open, this thread's allocations may wait for kept blocks, and released buffers
+// go back without a wait: for calls that wait for their stream before they return.  At its end
+// it waits once for the device if any came back, and when it is left by an exception, so that a
+// call that failed has nothing queued on the caller's arrays.
 class AllocScope {
  public:
   AllocScope() : thrown_(std::uncaught_exceptions()) { ++depth(); }
   ~AllocScope() {
-    int dev = 0;
-    if (--depth() == 0 && std::uncaught_exceptions() > thrown_ && hipGetDevice(&dev) == hipSuccess) wait_for_device(dev);
+    if (--depth() == 0) BlockCache::get().settle(std::uncaught_exceptions() > thrown_);
   }
   AllocScope(const AllocScope&) = delete;
   AllocScope& operator=(const AllocScope&) = delete;

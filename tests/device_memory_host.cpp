@@ -115,8 +115,7 @@ int release_waits() {
   return 0;
 }
 
-// ... a handle's buffers together once, and so does a setup that fails; one that does not fail
-// waits for its own stream by itself.
+// ... a handle's buffers together once, and so does a setup that gave buffers back or failed.
 int scopes_wait() {
   DevBuf<char> alive(256), many[5];
   for (auto& b : many) queue(0, (b.alloc(4096), b));
@@ -125,19 +124,20 @@ int scopes_wait() {
     for (auto& b : many) b.release();
   }
   CHECK(model.in_use[0].empty() && model.waits[0] == 1);
-  for (const bool fails : {false, true}) {
-    DevBuf<char> caller(512);
+  for (int kind = 0; kind < 3; ++kind) {  // gives nothing back; gives a buffer back; fails
+    DevBuf<char> caller(512), kept;
     try {
       AllocScope outer;
       {
         AllocScope inner;
-        DevBuf<char> b(100 << 10);
+        kept.alloc(100 << 10);
+        if (kind == 1) kept.release();
       }
       queue(0, caller);
-      if (fails) blk::fail(BLKAMG_EINVAL, "as a setup would");
+      if (kind == 2) blk::fail(BLKAMG_EINVAL, "as a setup would");
     } catch (const blk::Error&) {
     }
-    CHECK(busy(caller) == !fails);
+    CHECK(busy(caller) == (kind == 0));
     model.in_use[0].clear();
   }
   return 0;
@@ -159,6 +159,33 @@ int refused_waits() {
   AllocScope scope;
   DevBuf<char> c(1 << 20);
   CHECK(c.p == p && !busy(c));
+  return 0;
+}
+
+// A program that sets up, solves with vectors allocated outside the setup, and destroys, again
+// and again: the first round's memory serves all.
+int rounds() {
+  DevBuf<char> alive(256);
+  int first = 0;
+  for (int round = 0; round < 20; ++round) {
+    DevBuf<char> plan, vec[2];
+    {
+      AllocScope setup;
+      DevBuf<char> scratch(3 << 20);
+      queue(0, scratch);
+      plan.alloc(5 << 20);
+    }
+    for (auto& v : vec) {
+      v.alloc(9 << 20);
+      CHECK(!busy(v));
+      queue(0, v);
+    }
+    blk::FreeScope destroy;
+    plan.release();
+    for (auto& v : vec) v.release();
+    if (round == 0) first = model.mallocs;
+  }
+  CHECK(model.mallocs == first && model.frees == 0);
   return 0;
 }
 
@@ -230,6 +257,7 @@ int main(int argc, char** argv) {
                                                 {"release_waits", release_waits},
                                                 {"scopes_wait", scopes_wait},
                                                 {"refused_waits", refused_waits},
+                                                {"rounds", rounds},
                                                 {"bound", bound},
                                                 {"given_back", given_back}};
   const auto it = argc == 2 ? all.find(argv[1]) : all.end();

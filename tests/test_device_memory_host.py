@@ -22,7 +22,7 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["two_devices", "release_waits", "scopes_wait", "refused_waits",
-                                      "bound", "given_back"])
+                                      "rounds", "bound", "given_back"])
 def test_scenario(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
