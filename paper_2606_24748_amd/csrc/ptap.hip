@@ -505,12 +505,19 @@ bool ap_cheaper(const PtapPlan& pl, const bsr_s* A, const bsr_s* P) {
          static_cast<double>(A->nnzb) * (A->br * A->br * vs + 4.0);
 }
 
-// The brick tables where the patterns suit (false: the two passes), and the A P scratch (with
-// bricks only where A P is wanted).  BLKAMG_PTAP_TUNE "nobrick" keeps the two passes.
+// The brick tables where the patterns suit and memory allows (false: the two passes), and the
+// A P scratch (with bricks only where A P is wanted).  BLKAMG_PTAP_TUNE "nobrick" keeps the two
+// passes.
 bool finish_plan(PtapPlan& pl, const bsr_s* A, const bsr_s* P, const bsr_s* C, bool want_ap, bool no_brick,
                  hipStream_t s) {
   const bool keep = want_ap && ap_cheaper(pl, A, P);
-  if (no_brick || !brick_symbolic(A, P, C, pl, keep, s)) pl.brick = BrickPlan{};
+  bool on = false;
+  try {
+    on = !no_brick && brick_symbolic(A, P, C, pl, keep, s);
+  } catch (const Error& e) {
+    if (e.code != BLKAMG_ENOMEM) throw;
+  }
+  if (!on) pl.brick = BrickPlan{};
   if (!pl.brick.on || pl.brick.keep_ap)
     pl.ap_val.alloc(static_cast<size_t>(pl.ap_nslots) * P->br * P->bc * (A->dtype == BLKAMG_F64 ? 8 : 4));
   return pl.brick.on;
