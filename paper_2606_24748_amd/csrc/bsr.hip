@@ -97,16 +97,16 @@ int lanes_for(const bsr_s* A, int nrhs) {
   const double avg = A->avg_blocks_per_row();
   const size_t vb = A->block_elems() * dtype_size(A->dtype);  // bytes per block
   if (nrhs > 1) {
-    // Eight right-hand sides, measured at 64^3 nodes (FP64 / FP32, us).  Few blocks per row
-    // (prolongators, 4.5): 8 x 1 42 / 25 against 48 / 34 with 16 x 1.  27 per row: 16 x 2,
-    // 162 / 84 against 193 / 91 with 8 lanes and 171 / 93 with 32 x 2 (6x6: 20 / 14 against
-    // 23-30 / 14-18).  Long rows of 3x3 blocks (triquadratic, 62 per row): 64 x 1 in FP64
-    // (164 against 175 with 32 x 1), 32 x 1 in FP32 (90 against 101).  Restrictions (106-121):
-    // 64 x 2, 43 / 28 against 46 / 26 with 16 x 2 there but 33 / 22 against 102 / 56 where
-    // there are few rows.
+    // Eight right-hand sides: the shapes whose chains (kChains) are those of one lane per block,
+    // measured at 64^3 nodes (FP64 / FP32, us).  Prolongators, 4.5 blocks per row: 8 x 1, 45 / 31
+    // against 58 / 48 with 16 x 1.  12 per row (3x3): 16 x 1 in FP64 (87 against 97 with 8 x 1), 8 x
+    // 1 in FP32 (35 against 48).  27: 32 x 1 in FP64 (179; 16 x 1 takes 164, but chains two blocks),
+    // 16 x 1 in FP32 (88 against 118 with 32 x 1) and for 6x6 blocks in FP64 (20.4 against 21.7 with
+    // 16 x 2).  Triquadratic rows, 62: 64 x 1 in FP64 (173 against 180 with 32 x 1), 32 x 1 in FP32
+    // (97 against 122 with 64 x 1).  Restrictions, 106 - 121: 64 x 2, 50 / 31.
     if (avg <= 8.0) return lane_code(8, 1);
-    if (avg <= 16.0) return lane_code(16, 1);
-    if (avg <= 40.0) return lane_code(16, 2);
+    if (avg <= 16.0) return lane_code(A->dtype == BLKAMG_F64 ? 16 : 8, 1);
+    if (avg <= 40.0) return A->dtype == BLKAMG_F64 && vb < 288 ? lane_code(32, 1) : lane_code(16, 1);
     if (A->block_elems() >= 18) return lane_code(64, 2);
     return A->dtype == BLKAMG_F64 ? lane_code(64, 1) : lane_code(32, 1);
   }

@@ -211,81 +211,101 @@ __device__ __forceinline__ void panel_fma(const TA (&raw)[PER], const TA (&xv)[B
   }
 }
 
-// G lanes per block row: G / CL block slots of CL lanes.  Slot s takes blocks s, s + S, ...
-// (U at a time), its CL lanes load the block's values in CL pieces and 16 bytes each of
-// the BC panel rows, and pass the values around by quad permutations.  A load instruction
-// of a wave so covers the whole 64- or 32-byte panel rows of 16 or 32 blocks, where one
-// lane per block touched 64 different lines for 16 bytes each: the kernel was bound by
-// those L1 accesses.  The S partial sums are added by an xor tree; every lane then holds
-// its columns of all BR rows, and slot s finishes rows s, s + S, ...
-// 262,144 rows of 27 3x3 blocks: FP64 248 -> 162 us (3.8 TB/s on the bytes of A, x and y),
-// FP32 116 -> 84; its prolongator 79 -> 42 and restriction 95 -> 43 us in FP64.
+// The partial sums of a lane: its columns of the row's BR entries.
+template <int BR, int CPL, class TA>
+struct ColSums {
+  TA v[BR][CPL];
+  __device__ __forceinline__ void add(const ColSums& o) {
+#pragma unroll
+    for (int i = 0; i < BR; ++i)
+#pragma unroll
+      for (int q = 0; q < CPL; ++q) v[i][q] += o.v[i][q];
+  }
+};
+
+// A row's blocks are added as V lanes with one chain of blocks each would (block k on chain
+// k % V), in xor-tree order: whatever G is, FP32 and FP64 take as many roundings as with one
+// lane per block.  Adding a slot's blocks one after the other instead was 8 % faster (27 3x3
+// blocks: FP64 162 us, FP32 84) and 5 % (FP32) and 1.5 % (FP64) further from the exact product.
+template <class TX, int G, int U>
+constexpr int kChains = U == 1 && sizeof(TX) == 4 ? 2 * G : G;
+
+// G lanes per block row: G / CL block slots of CL lanes.  The V chains of a row are dealt to
+// the S slots, T = V / S each; a slot's CL lanes load a block's values in CL pieces and 16
+// bytes each of the BC panel rows, and pass the values around by quad permutations.  A load
+// instruction of a wave so covers the whole 64- or 32-byte panel rows of 16 or 32 blocks, where
+// one lane per block touched 64 different lines for 16 bytes each: the kernel was bound by
+// those L1 accesses.  The tree's upper levels join a slot's chains, the lower ones the slots;
+// every lane then holds its columns of all BR rows, and slot s finishes rows s, s + S, ...
+// 262,144 rows of 27 3x3 blocks: FP64 248 -> 179 us (3.5 TB/s on the bytes of A, x and y), FP32
+// 116 -> 88; its prolongator 79 -> 45 and restriction 95 -> 50 us in FP64.  The vector units
+// bound it as much as the loads do, so the chains are loops and the 3x3 kernel is held to 72
+// registers (seven waves a SIMD): unrolled it takes 138, or 72 with spills, and 265 us.
 template <int BR, int BC, int G, int U, class TM, class TX, class TA, class Epi>
-__global__ __launch_bounds__(kBlock) void spmm8_kernel(int nbr, const int32_t* __restrict__ rowptr,
-                                                       const int32_t* __restrict__ colidx,
-                                                       const TM* __restrict__ val,
-                                                       const TX* __restrict__ x, Epi epi) {
+__global__ __launch_bounds__(kBlock, BR * BC == 9 && U == 1 ? 7 : 1) void spmm8_kernel(
+    int nbr, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx, const TM* __restrict__ val,
+    const TX* __restrict__ x, Epi epi) {
   constexpr int CL = kColLanes<TX>, CPL = 8 / CL, S = G / CL;
   constexpr int BE = BR * BC, PER = (BE + CL - 1) / CL;
-  static_assert(G % CL == 0 && S >= 1, "a block row needs at least one slot");
+  constexpr int V = kChains<TX, G, U>, T = V / S;
+  static_assert(G % CL == 0 && (T == 2 || T == 4), "a slot takes two or four chains");
+  using Sums = ColSums<BR, CPL, TA>;
   constexpr int kRows = kBlock / G;
   const int lb = xcd_chunked_block(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x), kSpmvChunk);
   const int row = lb * kRows + static_cast<int>(threadIdx.x) / G;
   const int lane = static_cast<int>(threadIdx.x) % G;
   const int slot = lane / CL, cl = lane % CL;
   const int piece = cl * PER < BE - PER ? cl * PER : BE - PER;  // the lane's values of a block
-  TA acc[BR][CPL];
-#pragma unroll
-  for (int i = 0; i < BR; ++i)
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) acc[i][q] = TA(0);
+  Sums sum{};
   const bool active = row < nbr;
   if (active) {
     const int k1 = rowptr[row + 1];
-    for (int kb = rowptr[row] + slot; kb < k1; kb += S * U) {
-      TM raw[U][PER];
-      TA xv[U][BC][CPL];
+    const int k0 = rowptr[row] + slot;
+#pragma unroll 1
+    for (int h = 0; h < T / 2; ++h) {
+      Sums pair{};
+#pragma unroll 1
+      for (int t = h; t < T; t += T / 2) {
+        Sums chain{};
+#pragma unroll 1
+        for (int kb = k0 + t * S; kb < k1; kb += V * U) {
+          TM raw[U][PER];
+          TA xv[U][BC][CPL];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int k = kb + u * S;
-        if (k < k1) {
-          const TX* xc = x + static_cast<size_t>(colidx[k]) * (BC * 8) + cl * CPL;
-          const TM* b = val + static_cast<size_t>(k) * BE + piece;
+          for (int u = 0; u < U; ++u) {
+            const int k = kb + u * V;
+            if (k < k1) {
+              const TX* xc = x + static_cast<size_t>(colidx[k]) * (BC * 8) + cl * CPL;
+              const TM* b = val + static_cast<size_t>(k) * BE + piece;
 #pragma unroll
-          for (int t = 0; t < PER; ++t) raw[u][t] = b[t];
+              for (int e = 0; e < PER; ++e) raw[u][e] = b[e];
 #pragma unroll
-          for (int j = 0; j < BC; ++j) ld_cols<TA>(xc + j * 8, xv[u][j]);
-        } else {
+              for (int j = 0; j < BC; ++j) ld_cols<TA>(xc + j * 8, xv[u][j]);
+            } else {
 #pragma unroll
-          for (int t = 0; t < PER; ++t) raw[u][t] = TM{};
+              for (int e = 0; e < PER; ++e) raw[u][e] = TM{};
 #pragma unroll
-          for (int j = 0; j < BC; ++j)
+              for (int j = 0; j < BC; ++j)
 #pragma unroll
-            for (int q = 0; q < CPL; ++q) xv[u][j][q] = TA(0);
+                for (int q = 0; q < CPL; ++q) xv[u][j][q] = TA(0);
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            TA a[PER];
+#pragma unroll
+            for (int e = 0; e < PER; ++e) a[e] = ld<TA>(&raw[u][e]);
+            panel_fma<0, BE, BC, CL, PER, CPL, BR, TA>(a, xv[u], chain.v);
+          }
         }
+        pair.add(chain);
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        TA a[PER];
-#pragma unroll
-        for (int t = 0; t < PER; ++t) a[t] = ld<TA>(&raw[u][t]);
-        // every block's product is formed by itself, then added: a slot takes several blocks
-        // one after the other, and one long chain of roundings would cost FP32 12 % in error
-        TA part[BR][CPL];
-#pragma unroll
-        for (int i = 0; i < BR; ++i)
-#pragma unroll
-          for (int q = 0; q < CPL; ++q) part[i][q] = TA(0);
-        panel_fma<0, BE, BC, CL, PER, CPL, BR, TA>(a, xv[u], part);
-#pragma unroll
-        for (int i = 0; i < BR; ++i)
-#pragma unroll
-          for (int q = 0; q < CPL; ++q) acc[i][q] += part[i][q];
-      }
+      sum.add(pair);
     }
   }
+  TA (&acc)[BR][CPL] = sum.v;
 #pragma unroll
-  for (int off = CL; off < G; off <<= 1) {
+  for (int off = G / 2; off >= CL; off >>= 1) {
 #pragma unroll
     for (int i = 0; i < BR; ++i)
 #pragma unroll
