@@ -54,11 +54,11 @@ struct Level {
   DevBuf<int32_t> diag_idx;
   DevBuf<char> f, out, x, r, d, d2;    // work vectors [rows][vec_nr] (hierarchy dtype)
   int vec_nr = 0;
-  DevBuf<double> lz[6];                // Lanczos vectors (F64 hierarchies) ...
-  DevBuf<float> lzf[6];                // ... or F32
+  DevBuf<double> lz[4];                // Lanczos vectors (F64 hierarchies) ...
+  DevBuf<float> lzf[4];                // ... or F32
   // terminal segments: dense inverse Cholesky factors, all concatenated
   int n_term = 0, t_max_rows = 0, t_max_tiles = 0;
-  int64_t t_max_nn = 0, t_total = 0;
+  int64_t t_total = 0;
   DevBuf<int32_t> t_row0, t_nrows, t_ndof, t_dof_off;
   DevBuf<int64_t> t_mat_off;
   DevBuf<double> tL, tY, tYt, tct;
@@ -282,7 +282,6 @@ void finalize_level(amg_s* M, Level& L) {
   std::vector<int32_t> row0, nrows, ndof, dof_off{0};
   std::vector<int64_t> mat_off{0};
   L.t_max_rows = 0;
-  L.t_max_nn = 0;
   for (int t = L.n_act; t < ns; ++t) {
     const int32_t r0 = L.seg_off[t], nr = L.seg_off[t + 1] - L.seg_off[t];
     const int32_t nd = nr * L.bs;
@@ -292,7 +291,6 @@ void finalize_level(amg_s* M, Level& L) {
     dof_off.push_back(dof_off.back() + nd);
     mat_off.push_back(mat_off.back() + static_cast<int64_t>(nd) * nd);
     L.t_max_rows = std::max(L.t_max_rows, nr);
-    L.t_max_nn = std::max<int64_t>(L.t_max_nn, static_cast<int64_t>(nd) * nd);
   }
   mat_off.pop_back();
   L.t_max_tiles = (L.t_max_rows * L.bs + kT - 1) / kT;

@@ -21,7 +21,7 @@ constexpr int kMaxLanczos = 64;
 struct LevelScalars {
   double alpha[kMaxLanczos];
   double beta[kMaxLanczos];
-  double b0, inv_b, ratio;        // Lanczos: start norm; 1 / b_k and b_k / b_(k-1) of the current step
+  double inv_b, ratio;            // Lanczos: 1 / b_k and b_k / b_(k-1) of the current step
   double lam;                     // lambda_hat
   double coef[1 + 2 * kMaxCheb];  // 1/theta, then (c1, c2) per Chebyshev step
   double tmp[4];
@@ -119,7 +119,7 @@ struct OpLzNorm {
   __device__ void operator()(int s, int, double v) const {
     LevelScalars& S = sc[s];
     const double r = sqrt(v > 0.0 ? v : 0.0), b = r > 0.0 ? r : 1.0;
-    if (step < 0) S.b0 = b; else S.beta[step] = r;
+    if (step >= 0) S.beta[step] = r;
     S.ratio = step < 0 ? 0.0 : r * S.inv_b;
     S.inv_b = 1.0 / b;
   }

@@ -518,6 +518,7 @@ bool finish_plan(PtapPlan& pl, const bsr_s* A, const bsr_s* P, const bsr_s* C, b
     if (e.code != BLKAMG_ENOMEM) throw;
   }
   if (!on) pl.brick = BrickPlan{};
+  else pl.ap_pairs.codes.release();  // only the two passes read them
   if (!pl.brick.on || pl.brick.keep_ap)
     pl.ap_val.alloc(static_cast<size_t>(pl.ap_nslots) * P->br * P->bc * (A->dtype == BLKAMG_F64 ? 8 : 4));
   return pl.brick.on;
