@@ -49,20 +49,20 @@ METRIC = "PCG solve s + PtAP recompute s at 128^3 elasticity; %HBM peak; mixed v
 # valid only for the kernel sources it was measured on (their SHA-256 below), else
 # reported as null.  Summary and commands: profiles/bsr_spmv_fine_f64_128cube.md.
 TRAFFIC_RECORD = {
-    "sources_sha256": "892a7e82017996abe7144defdae117382aaddce8e76006c65a23a7a555f27c00",
-    "fetch_bytes": 3458992128,   # FETCH_SIZE 1,688,961 KiB x 2.00 (copy calibration)
-    "write_bytes": 53366784,     # WRITE_SIZE 52,116 KiB x 1.00
+    "sources_sha256": "444acf03b3f802e070b5170befb6256eb3dc002419fd75f391bdb91e8e016d32",
+    "fetch_bytes": 3458162688,   # FETCH_SIZE 1,688,556 KiB x 2.00 (copy calibration)
+    "write_bytes": 53350400,     # WRITE_SIZE 52,100 KiB x 1.00
 }
 TRAFFIC_SOURCES = ("paper_2606_24748_amd/csrc/spmv_core.hpp", "paper_2606_24748_amd/csrc/bsr.hip",
                    "paper_2606_24748_amd/csrc/common.hpp")
 
-# HBM traffic of one Galerkin recompute over all levels (FP64 hierarchy at 128^3: the
-# six pair-list passes), from the same kind of counter passes; null once its sources
-# change.  Summary: profiles/ptap_counters_128cube.md.
+# HBM traffic of one Galerkin recompute over all levels (FP64 hierarchy at 128^3: the fine
+# level's bricks and their sum, four pair-list passes), from the same kind of counter passes;
+# null once its sources change.  Summary: profiles/ptap_counters_128cube.md.
 PTAP_TRAFFIC_RECORD = {
-    "sources_sha256": "ad6696f0fa84ed15d7f74fa1396c3ee4378b199e4a69acbec0839a739ff6b56a",
-    "fetch_bytes": 34558126080,  # FETCH_SIZE 16,874,085 KiB x 2.00
-    "write_bytes": 5251006464,   # WRITE_SIZE 5,127,936 KiB x 1.00
+    "sources_sha256": "3fe37f0f617867db866cddd5709c82f72a79903d2322fc4aefbbb5fcecce66d9",
+    "fetch_bytes": 15200528384,  # FETCH_SIZE 7,422,133 KiB x 2.00
+    "write_bytes": 3086055424,   # WRITE_SIZE 3,013,726 KiB x 1.00
 }
 PTAP_TRAFFIC_SOURCES = ("paper_2606_24748_amd/csrc/ptap.hip", "paper_2606_24748_amd/csrc/ptap_brick.hip",
                         "paper_2606_24748_amd/csrc/ptap_plan.hpp",

@@ -339,7 +339,7 @@ struct EpiLanczos {
 // Largest eigenvalue of each segment's tridiagonal T_k by Sturm counts, then the
 // Chebyshev coefficients (Saad, Alg. 12.1) for [lo*lam, hi*lam].  One wave per segment: its
 // 64 lanes count at 64 points of the interval, which narrows it 65 times a round, so ten
-// rounds of k dependent divisions take the place of bisection's fifty (66 -> 10 us).
+// rounds of k dependent divisions take the place of bisection's fifty (66 -> 12 us).
 __global__ __launch_bounds__(64) void lanczos_finish_kernel(LevelScalars* sc, int k, const double* user_lam, double lo,
                                                             double hi, int degree) {
   const int sg = blockIdx.x, lane = threadIdx.x;

@@ -51,11 +51,12 @@ inline bool wait_for_device(int dev) {
   return ok;
 }
 
-// Freed blocks, kept for the setups and plans that come next.  A setup makes and frees some
-// 200 buffers; hipMalloc and hipFree take microseconds for a small one and 0.3 - 0.7 ms for
-// 50 - 130 MB, 9 ms of the 18 ms of an FP64 setup of a 40^3-element mesh.  With kept blocks
-// that setup takes 12.4 ms, an FP32 one 21 instead of 30, 64^3 36 instead of 47 (FP64).
-// Bounded per device by kHeld (a bound of 1 GiB left 64^3 at 43 ms) and a 64th of its memory.
+// Freed blocks, kept for the allocations that come next.  A setup makes and frees some 200
+// buffers; hipMalloc and hipFree take microseconds for a small one and 0.3 - 0.7 ms for 50 -
+// 130 MB.  Setup and destruction of a hierarchy without kept blocks -> with them, 40^3
+// elements: FP64 11.4 + 5.0 -> 7.4 + 0.2 ms, FP32 18 + 4.9 -> 11.1 + 0.3; 64^3: FP64 27.3 + 8.8
+// -> 19.5 + 0.3, FP32 62 + 10.7 -> 47 + 1.8.
+// Bounded per device by kHeld (1 GiB was too little for 64^3) and a 64th of its memory.
 // Given back when the last buffer of the library is freed, when hipMalloc or the caller's
 // allocator has no memory left, when the caller sets an allocator, and by blkamg_trim.  A block
 // is handed out after its device has been idle once since it came back, as it is after a
