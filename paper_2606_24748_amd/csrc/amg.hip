@@ -67,13 +67,13 @@ struct Level {
 
 struct GraphKey {
   const void* x = nullptr;
-  const void* A = nullptr;
+  const void* A[3] = {};  // its device arrays: another matrix may take a destroyed one's handle
   int nr = 0, unroll = 0, maxit = 0;
   double rtol = 0.0;
   uint64_t epoch = 0;
   bool operator==(const GraphKey& o) const {
-    return x == o.x && A == o.A && nr == o.nr && unroll == o.unroll && maxit == o.maxit && rtol == o.rtol &&
-           epoch == o.epoch;
+    return x == o.x && A[0] == o.A[0] && A[1] == o.A[1] && A[2] == o.A[2] && nr == o.nr && unroll == o.unroll &&
+           maxit == o.maxit && rtol == o.rtol && epoch == o.epoch;
   }
 };
 
@@ -1605,7 +1605,9 @@ template <int NR>
 void bpcg_graph(amg_s* M, bsr_s* A, double* x, double rtol, int maxit, int U) {
   GraphKey key;
   key.x = x;
-  key.A = A;
+  key.A[0] = A->rowptr;
+  key.A[1] = A->colidx;
+  key.A[2] = A->val;
   key.nr = NR;
   key.unroll = U;
   key.maxit = maxit;
